@@ -48,6 +48,10 @@ struct fc_graph {
     // marks them unusable; launches then start every problem with a search for heights in the kernel instead.
     bool labels_valid = false;         // d_labels / d_label_hmax may be used
     bool p1_valid = false;             // d_p1 / d_level_off / d_tree_ratio may be used
+    // Bit-row tables (graphs of at most 256 vertices): one block {heads [n][nw], adj [n][nw] as 64-bit words; records uint2
+    // [bitrow_rec]; row offsets int32 [n + 1]}, see BitRowGraph.  They follow the bandwidths: fc_graph_update_arcs writes them anew.
+    void *d_bitrow = nullptr;
+    int32_t bitrow_nw = 0, bitrow_rec = 0;   // 64-bit words per row, records
     void *d_edits = nullptr;           // int2 [edits_cap] {record, bandwidth}: staging for fc_graph_update_arcs
     size_t edits_cap = 0;
 };
@@ -57,6 +61,8 @@ struct fc_graph {
 // bandwidth later) instead of being dropped
 int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const int32_t *head,
                   const int32_t *bandwidth, const uint8_t *is_compute, fc_graph **out, bool keep_zero_links = false);
+// The bit-row tables of g as one block (layout: fc_graph::d_bitrow).  false: g has more than 256 vertices or 65535 records.
+bool fc_host_bitrow(const fc_graph *g, std::vector<uint64_t> &block, int32_t *nw, int32_t *n_rec);
 // Set the bandwidth of existing links on the host side of g (records, in-bandwidths, the facts fc_graph_info reports).
 // Either every update is applied or none; `edits` receives {record, new bandwidth} for both records of every link
 // whose bandwidth changed.

@@ -1,0 +1,91 @@
+"""GPU tests of the bit-row solver (graphs of at most 256 vertices): every number of words per row and the edges between
+them, one vertex beyond, both kinds of multiplier, weights, in-place updates, and the other solver on the same graphs."""
+import numpy as np
+import pytest
+
+import oracle as o
+import workloads as w
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():          # selected explicitly on a machine without a GPU
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2402_06787_amd as fc   # noqa: E402
+
+DEV = torch.device("cuda:0")
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(DEV)
+
+
+def _random_topology(rng, n, degree):
+    """A ring and random arcs, about a third of them with the link back; one vertex joined to everybody (rows longer than a
+    wavefront on the larger graphs)."""
+    t, h = [], []
+    for u in range(n):
+        heads = {(u + 1) % n} | set(rng.integers(0, n, degree).tolist())
+        if u == 0:
+            heads |= set(range(n))
+        for v in sorted(heads - {u}):
+            t.append(u); h.append(v)
+            if rng.random() < 0.35:
+                t.append(v); h.append(u)
+    isc = np.zeros(n, np.uint8)
+    isc[rng.permutation(n)[:max(2, int(n * rng.uniform(0.5, 1.0)))]] = 1
+    return w.Topology(f"r{n}", n, np.array(t, np.int32), np.array(h, np.int32), rng.integers(1, 30, len(t)).astype(np.int32), isc)
+
+
+@pytest.mark.parametrize("n", [2, 3, 63, 64, 65, 127, 128, 129, 192, 193, 255, 256, 257])
+def test_values_match_the_oracle_at_the_edges_of_the_row_words(n):
+    rng = np.random.default_rng(1000 + n)
+    for degree in (1, 6):
+        topo = _random_topology(rng, n, degree)
+        P, N = 120, topo.n_compute
+        sink = rng.integers(0, n, P).astype(np.int32)
+        k = rng.integers(1, 9, P).astype(np.int32)
+        k[::5] = (2 ** 31 - 1) // N                       # the largest flows there are: sums of two residuals pass 2^31
+        U = np.maximum(1, k.astype(np.int64) * N // 40 * rng.integers(1, 80, P) // 30).clip(1, 2 ** 30).astype(np.int32)
+        den = rng.integers(1, 90, P).astype(np.int32)     # many capacities round down to nothing
+        want = o.aux_maxflow_batch(topo, sink, U, k, threads=16)
+        with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+            for stats in (False, True):
+                got, st = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k), want_stats=stats)
+                assert (got.cpu().numpy().astype(np.int64) == want).all(), (n, degree, stats)
+            assert st["not_converged"] == 0
+            other, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k), options={"force_wide": 1})
+            assert (other.cpu().numpy() == want).all(), (n, degree)
+            small = k < 1000                              # (the product num * b stays within the entry point's bounds)
+            got, _ = fc.fc_maxflow_batch_floor(g, _dev(sink[small]), _dev(U[small]), _dev(den[small]), _dev(k[small]))
+            ref = o.aux_maxflow_batch_floor(_merge(topo), sink[small], U[small], den[small], k[small], threads=16)
+            assert (got.cpu().numpy().astype(np.int64) == ref).all(), (n, degree)
+
+
+def _merge(topo):
+    acc = {}
+    for a, b, c in zip(topo.tail.tolist(), topo.head.tolist(), topo.bandwidth.tolist()):
+        acc[(a, b)] = acc.get((a, b), 0) + c
+    keys = sorted(acc)
+    return w.Topology(topo.name, topo.n_vertices, np.array([a for a, _ in keys], np.int32), np.array([b for _, b in keys], np.int32),
+                      np.array([acc[x] for x in keys], np.int32), topo.is_compute)
+
+
+@pytest.mark.parametrize("n", [40, 150])
+def test_updated_links_and_weights_reach_the_bit_rows(n):
+    rng = np.random.default_rng(n)
+    topo = _merge(_random_topology(rng, n, 3))
+    P = 100
+    sink = rng.integers(0, n, P).astype(np.int32); k = rng.integers(1, 6, P).astype(np.int32); U = rng.integers(1, 12, P).astype(np.int32)
+    with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        hit = rng.permutation(len(topo.tail))[: len(topo.tail) // 4]
+        bw = topo.bandwidth.copy(); bw[hit] = rng.integers(0, 40, len(hit))
+        fc.fc_graph_update_arcs(g, topo.tail[hit], topo.head[hit], bw[hit], refresh_tables=False)
+        after = w.Topology("after", n, topo.tail, topo.head, bw, topo.is_compute)
+        got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k))
+        assert (got.cpu().numpy() == o.aux_maxflow_batch(after, sink, U, k, threads=16)).all()
+        wts = rng.integers(0, 4, n).astype(np.int32); wts[np.flatnonzero(topo.is_compute)[0]] = 2
+        fc.fc_graph_set_source_weights(g, wts)
+        got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k))
+        assert (got.cpu().numpy() == o.weighted_aux_maxflow_batch(after, sink, U, k, wts)).all()
