@@ -89,3 +89,41 @@ def test_updated_links_and_weights_reach_the_bit_rows(n):
         fc.fc_graph_set_source_weights(g, wts)
         got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k))
         assert (got.cpu().numpy() == o.weighted_aux_maxflow_batch(after, sink, U, k, wts)).all()
+
+
+def _scaled_rail_fabric(boxes, per_box, caps, U):
+    """An Eulerian cluster (boxes around a switch, one rail per place in a box) with one bandwidth inside per box, times U."""
+    n_compute = boxes * per_box
+    t, h, b = [], [], []
+    for c in range(n_compute):
+        for a, v, x in ((c, n_compute + c // per_box, caps[c // per_box]), (c, n_compute + boxes + c % per_box, 2)):
+            t += [a, v]; h += [v, a]; b += [x * U, x * U]
+    isc = np.zeros(n_compute + boxes + per_box, np.uint8); isc[:n_compute] = 1
+    return w.Topology("rails", len(isc), np.array(t, np.int32), np.array(h, np.int32), np.array(b, np.int32), isc)
+
+
+@pytest.mark.parametrize("boxes,per_box", [(3, 2), (12, 4), (16, 7), (22, 8)])     # 1, 2, 3 and 4 words per row
+def test_edge_splitting_on_bit_rows_agrees_with_the_other_solver(boxes, per_box):
+    rng = np.random.default_rng(boxes)
+    k = 2
+    D = _scaled_rail_fabric(boxes, per_box, 2 * rng.integers(10, 17, boxes), boxes - 1)     # optimum (boxes - 1) / 2
+    n, isc = D.n_vertices, D.is_compute
+    into = np.flatnonzero(isc[D.head] == 0)
+    pairs = []
+    for _ in range(24):
+        e = int(rng.choice(into)); out = np.flatnonzero(D.tail == D.head[e])
+        pairs.append((D.tail[e], D.head[e], D.head[int(rng.choice(out))]))
+    pairs += [(0, 1, 2), (0, n - 1, n), (0, n - 1, n - 1)]                                  # no pair of links through a switch
+    d = [_dev(x) for x in zip(*pairs)]
+    with fc.fc_graph_upload(n, D.tail, D.head, D.bandwidth, isc) as g:
+        for flows in (False, True):
+            here = fc.fc_split_gamma_batch(g, 1, k, *d, want_flows=flows, want_stats=True)
+            there = fc.fc_split_gamma_batch(g, 1, k, *d, want_flows=flows, options={"split_two_launches": 2})
+            assert torch.equal(here["gamma"], there["gamma"]), (here["gamma"], there["gamma"])
+            assert here["stats"]["not_converged"] == 0 and int((here["gamma"] > 0).sum()) > 0
+            if flows:
+                assert torch.equal(here["flows"], there["flows"])
+    if boxes <= 16:
+        here = fc.fc_remove_switches(n, D.tail, D.head, D.bandwidth, isc, k)
+        there = fc.fc_remove_switches(n, D.tail, D.head, D.bandwidth, isc, k, options={"split_two_launches": 1})
+        assert here["links"] == there["links"] and here["table"] == there["table"]
