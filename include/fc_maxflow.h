@@ -450,7 +450,10 @@ const char *fc_strerror(int code);
  * ahead: it also evaluates the states that follow (options->tree_chain_states of them in all) if, each time,
  * the first link that was neither rejected before nor zero the last time any root-set tried it is accepted in
  * full; those results are used as far as the guesses turn out right.  A link whose mu was 0 is
- * not tried again while the same root-set grows (its mu cannot rise).  Unless options->tree_warm_start is 2
+ * not tried again while the same root-set grows (its mu cannot rise).  On at most 256 vertices, until the first
+ * copy is made and unless an option of the other solver is set, it works the other way round: it grows many trees by the
+ * links that no known cut forbids, asks one launch which cuts that breaks, and takes back what does (n_batches then
+ * counts the links of every root-set in batches of tree_chain_states).  Otherwise, unless options->tree_warm_start is 2
  * the launches do not start from nothing: the flow that brings the other root-sets' demands to a vertex y
  * is kept in device memory (n_vertices rows of one value per link, and as many again per state a launch looks
  * ahead: fewer states are looked ahead when that would exceed 2 GiB), a max-flow into y repairs it for the capacities used

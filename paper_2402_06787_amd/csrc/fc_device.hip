@@ -20,6 +20,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <array>
 #include <cstdio>
 #include <cstdlib>
 #include <cstring>
@@ -27,6 +28,7 @@
 #include <new>
 #include <map>
 #include <set>
+#include <unordered_set>
 #include <vector>
 
 #include "fc_internal.h"
