@@ -590,10 +590,10 @@ def fc_remove_switches(n_vertices, tail, head, capacity, is_compute, k: int, str
             continue
         break
     _check(rc, "fc_remove_switches")
-    links = {(int(ot[i]), int(oh[i])): int(oc[i]) for i in range(n_out.value)}
+    links = dict(zip(zip(ot[:n_out.value].tolist(), oh[:n_out.value].tolist()), oc[:n_out.value].tolist()))
     table = {}
-    for i in range(n_routes.value):
-        table.setdefault((int(ru[i]), int(rt[i])), {})[int(rw[i])] = int(ra[i])
+    for u, t, w, amount in zip(*(x[:n_routes.value].tolist() for x in (ru, rt, rw, ra))):
+        table.setdefault((u, t), {})[w] = amount
     return {"links": links, "table": table, "batches": int(batches.value)}
 
 
@@ -649,5 +649,5 @@ def fc_construct_trees(n_vertices, links, k: int, stream=None, options=None):
     trees = []
     for i in range(n_trees.value):
         lo = i * (n - 1)
-        trees.append((int(root[i]), int(mult[i]), [(int(exs[lo + q]), int(eys[lo + q])) for q in range(n - 1)]))
+        trees.append((int(root[i]), int(mult[i]), list(zip(exs[lo:lo + n - 1].tolist(), eys[lo:lo + n - 1].tolist()))))
     return {"trees": trees, "batches": int(batches.value)}
