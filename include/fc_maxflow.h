@@ -411,8 +411,9 @@ int fc_split_gamma_batch(const fc_graph *g, int32_t U, int32_t k, int64_t n_pair
  * compute-only digraph D* and the path recovery table as rows (u, t, w, amount): `amount` of the capacity of
  * (u, t) was routed through switch w.  *n_out / *n_routes receive the row counts; if a capacity argument is too
  * small the call returns FC_EWORKSPACE with the counts set and nothing else written.  n_batches_or_null counts the
- * gamma launches.  Every batch re-uploads the current graph, so this is a driver for graphs that fit the 32-bit
- * on-chip state, not a tuned stage.  Errors: FC_EINVAL (also: D not Eulerian), FC_ENOCONVERGE (an egress link
+ * launches: on at most 256 vertices, unless an option of the other solver is set, the host splits off what the cuts it
+ * knows allow and asks a launch which cuts that breaks; otherwise every batch of gamma max-flows re-uploads the
+ * current graph.  Errors: FC_EINVAL (also: D not Eulerian), FC_ENOCONVERGE (an egress link
  * could not be used up: min_v F(s, v) >= N k did not hold in D), FC_EOVERFLOW, FC_EUNSUPPORTED, FC_EDEVICE, FC_ENOMEM. */
 int fc_remove_switches(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const int32_t *head,
                        const int32_t *capacity, const uint8_t *is_compute, int32_t k,

@@ -127,3 +127,56 @@ def test_edge_splitting_on_bit_rows_agrees_with_the_other_solver(boxes, per_box)
         here = fc.fc_remove_switches(n, D.tail, D.head, D.bandwidth, isc, k)
         there = fc.fc_remove_switches(n, D.tail, D.head, D.bandwidth, isc, k, options={"split_two_launches": 1})
         assert here["links"] == there["links"] and here["table"] == there["table"]
+
+
+@pytest.mark.parametrize("boxes,per_box", [(10, 5), (42, 2), (12, 9), (31, 7)])    # 65, 128, 129 and 255 vertices
+def test_switch_removal_by_cuts_agrees_with_the_other_solver(boxes, per_box):
+    k = 2
+    D = _scaled_rail_fabric(boxes, per_box, 2 * np.random.default_rng(boxes).integers(10, 17, boxes), boxes - 1)
+    args = (D.n_vertices, D.tail, D.head, D.bandwidth, D.is_compute)
+    here = fc.fc_remove_switches(*args, k)
+    there = fc.fc_remove_switches(*args, k, options={"split_two_launches": 2})
+    assert here["links"] == there["links"] and here["table"] == there["table"]
+    for options in (None, {"split_two_launches": 2}):                                       # more than the fabric carries
+        with pytest.raises(fc.FcError) as err:
+            fc.fc_remove_switches(*args, k + 1, options=options)
+        assert err.value.code == fc.FC_ENOCONVERGE
+
+
+def test_a_switch_without_links_is_removed_whatever_the_others_carry():
+    isc = np.array([1, 1, 1, 0], np.uint8)
+    got = fc.fc_remove_switches(4, [0, 1, 2], [1, 2, 0], [1, 1, 1], isc, 5)
+    assert got["links"] == {(0, 1): 1, (1, 2): 1, (2, 0): 1} and got["table"] == {}
+
+
+def _ring_with_chords(n, k):
+    """A ring in both directions that carries k out-trees per root (two links into every interval), and some chords."""
+    rng = np.random.default_rng(n)
+    links = {(u, (u + d) % n): -(-(n - 1) * k // 2) for u in range(n) for d in (1, n - 1)}
+    for u, v in rng.integers(0, n, (n, 2)).tolist():
+        if u != v:
+            links[(u, v)] = links.get((u, v), 0) + int(rng.integers(1, 4))
+    return links
+
+
+@pytest.mark.parametrize("n,k", [(2, 1), (3, 1), (33, 1), (40, 2), (24, 3)])
+def test_trees_by_cuts_use_every_unit_and_agree_with_the_other_solver(n, k):
+    # one tree per root: never a copy; more than one: copies, and the construction changes over to the other solver
+    links = w.superposed_out_trees(n, k, 100 + n)
+    here = fc.fc_construct_trees(n, links, k)
+    there = fc.fc_construct_trees(n, links, k, options={"threads_per_problem": 64})
+    assert here["trees"] == there["trees"]
+    short = dict(links)
+    short[max(short, key=lambda e: (short[e], e))] -= 1                                     # every unit was needed
+    for options in (None, {"threads_per_problem": 64}):
+        with pytest.raises(fc.FcError) as err:
+            fc.fc_construct_trees(n, short, k, options=options)
+        assert err.value.code == fc.FC_ENOCONVERGE
+
+
+@pytest.mark.parametrize("n,k", [(63, 1), (64, 2), (65, 1), (128, 1), (129, 1), (193, 1), (256, 1)])
+def test_trees_by_cuts_agree_with_the_other_solver_at_the_edges_of_the_row_words(n, k):
+    links = _ring_with_chords(n, k)
+    here = fc.fc_construct_trees(n, links, k)
+    there = fc.fc_construct_trees(n, links, k, options={"threads_per_problem": 64})
+    assert here["trees"] == there["trees"]
