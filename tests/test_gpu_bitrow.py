@@ -63,6 +63,24 @@ def test_values_match_the_oracle_at_the_edges_of_the_row_words(n):
             assert (got.cpu().numpy().astype(np.int64) == ref).all(), (n, degree)
 
 
+@pytest.mark.parametrize("n", [40, 150])
+def test_a_broken_source_bound_is_refused(n):
+    # N * bound fits 16 bits: a problem within the bound, one above it that still fits, and demands beyond 16 bits
+    topo = _random_topology(np.random.default_rng(n), n, 3)
+    N = topo.n_compute
+    k = np.array([1, 2, 65535 // N, 65535 // N + 1, 10 * (65535 // N)], np.int32)
+    sink, U = np.full(5, topo.compute_nodes[0], np.int32), np.full(5, 7, np.int32)
+    want = o.aux_maxflow_batch(topo, sink, U, k, threads=4).tolist()[:3] + [fc.FC_FLOW_UNSUPPORTED] * 2
+    with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for solver in ({}, {"global_relabel_steps": 32}):
+            for stats in (False, True):
+                got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k), options={"src_cap_bound": 1, **solver}, want_stats=stats)
+                assert got.cpu().tolist() == want, (solver, stats)
+            r = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=True, options={"src_cap_bound": 1, **solver})
+            assert (r["flows"].cpu().numpy()[3:] == fc.FC_FLOW_UNSUPPORTED).all() and r["feasible"].cpu().tolist()[3:] == [0, 0]
+            assert (r["flows"].cpu().numpy()[:3] > 0).all()
+
+
 def _merge(topo):
     acc = {}
     for a, b, c in zip(topo.tail.tolist(), topo.head.tolist(), topo.bandwidth.tolist()):
