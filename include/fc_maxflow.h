@@ -162,7 +162,7 @@ int fc_graph_free(fc_graph *g);
  * gamma, c(u, t) goes up by gamma -- and asks for max-flows on the changed graph right away; what-if questions about a
  * degraded or upgraded link are of the same kind.  This call rewrites the bandwidth of existing links where they
  * lie: the residual CSR keeps its shape, its record numbering (fc_graph_csr) and its device addresses, and nothing
- * is allocated beyond a staging list of 8 bytes per changed record that the graph keeps for later calls.
+ * is allocated beyond a staging list of 32 bytes per update that the graph keeps for later calls.
  *
  * tail, head, bandwidth: host int32 [n_updates].  Link (tail[i], head[i]) -- one ordered vertex pair, as after the
  * merging of parallel arcs -- gets the bandwidth bandwidth[i] >= 0 (the new value, not a difference; when a link is
@@ -183,9 +183,9 @@ int fc_graph_free(fc_graph *g);
  * is up to date.  Must not run concurrently with other calls on the same graph.  A graph from fc_graph_build gets
  * the host part only.
  * Errors: FC_EINVAL (null pointers, ids out of range, negative bandwidth, a link the graph does not have,
- * refresh_tables not 0 or 1), FC_EOVERFLOW (an in-bandwidth sum reaches 2^31) -- in both cases nothing was changed;
- * FC_ENOMEM; FC_EDEVICE (also: the graph lives on another GPU than the current one) -- after a device error during
- * the update the graph must only be freed. */
+ * refresh_tables not 0 or 1), FC_EOVERFLOW (an in-bandwidth sum reaches 2^31), FC_ENOMEM without refresh_tables -- in these
+ * cases nothing was changed; FC_EDEVICE (also: the graph lives on another GPU than the current one) -- after a device error
+ * during the update the graph must only be freed. */
 int fc_graph_upload_with_spares(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const int32_t *head,
                                 const int32_t *bandwidth, const uint8_t *is_compute, fc_graph **out);
 int fc_graph_update_arcs(fc_graph *g, int64_t n_updates, const int32_t *tail, const int32_t *head,

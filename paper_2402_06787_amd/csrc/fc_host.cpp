@@ -108,38 +108,53 @@ int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const
 // ---------------------------------------------------------------------------------------------
 // Tables of the bit-row solver: per vertex the neighbours in either direction by increasing id, one record each with the
 // bandwidth towards the neighbour (0: there is only the link back) and the place of the opposite record.
-bool fc_host_bitrow(const fc_graph *g, std::vector<uint64_t> &block, int32_t *nw_out, int32_t *n_rec_out) {
+int32_t fc_bitrow_lay_down(int32_t n, std::vector<uint64_t> &block) {
+    const int32_t nw = (n + 63) / 64;
+    const size_t words = size_t(n) * size_t(nw);
+    std::vector<int32_t> row(size_t(n) + 1, 0);
+    for (int32_t u = 0; u < n; ++u) {
+        row[size_t(u) + 1] = row[size_t(u)];
+        for (int32_t j = 0; j < nw; ++j) row[size_t(u) + 1] += __builtin_popcountll(block[words + size_t(u) * size_t(nw) + size_t(j)]);
+    }
+    const int32_t n_rec = row[size_t(n)];
+    if (n_rec > 65535) return -1;
+    block.resize(2 * words + size_t(n_rec) + (size_t(n) + 2) / 2, 0);
+    const uint64_t *adj = block.data() + words;
+    uint64_t *rec = block.data() + 2 * words;
+    std::memcpy(rec + n_rec, row.data(), sizeof(int32_t) * (size_t(n) + 1));
+    for (int32_t u = 0, r = 0; u < n; ++u)                          // by increasing u, the records of w get to u in order
+        for (int32_t j = 0; j < nw; ++j)
+            for (uint64_t m = adj[size_t(u) * size_t(nw) + size_t(j)]; m; m &= m - 1, ++r) {
+                const int32_t w = j * 64 + __builtin_ctzll(m);
+                rec[r] = uint64_t(uint32_t(row[size_t(w)]++) | uint32_t(w) << 16 | uint32_t(u) << 24) << 32;
+            }
+    return n_rec;
+}
+
+bool fc_host_bitrow(fc_graph *g, std::vector<uint64_t> &block, int32_t *nw_out, int32_t *n_rec_out) {
     const int32_t n = g->n;
     if (n > 256) return false;
     const int32_t nw = (n + 63) / 64;
-    std::vector<int32_t> b(size_t(n) * size_t(n), -1);              // -1: no neighbours
+    const size_t words = size_t(n) * size_t(nw);
+    block.assign(2 * words, 0);
     for (int32_t u = 0; u < n; ++u)
         for (int32_t r = g->row_ptr[size_t(u)]; r < g->row_ptr[size_t(u) + 1]; ++r) {
-            int32_t &x = b[size_t(u) * size_t(n) + size_t(g->other[size_t(r)])];
-            if (g->fwd[size_t(r)]) x = g->bw[size_t(r)]; else if (x < 0) x = 0;
-        }
-    std::vector<int32_t> row(size_t(n) + 1, 0), at(size_t(n) * size_t(n), 0);
-    for (int32_t u = 0; u < n; ++u) {
-        int32_t c = row[size_t(u)];
-        for (int32_t w = 0; w < n; ++w) if (b[size_t(u) * size_t(n) + size_t(w)] >= 0) at[size_t(u) * size_t(n) + size_t(w)] = c++;
-        row[size_t(u) + 1] = c;
-    }
-    const int32_t n_rec = row[size_t(n)];
-    if (n_rec > 65535) return false;
-    const size_t words = size_t(n) * size_t(nw);
-    block.assign(2 * words + size_t(n_rec) + (size_t(n) + 2) / 2, 0);
-    uint64_t *heads = block.data(), *adj = heads + words, *rec = adj + words;
-    for (int32_t u = 0; u < n; ++u)
-        for (int32_t w = 0; w < n; ++w) {
-            const int32_t x = b[size_t(u) * size_t(n) + size_t(w)];
-            if (x < 0) continue;
+            const int32_t w = g->other[size_t(r)];
+            const size_t at = size_t(u) * size_t(nw) + size_t(w >> 6);
             const uint64_t bit = uint64_t(1) << (w & 63);
-            if (x > 0) heads[size_t(u) * size_t(nw) + size_t(w >> 6)] |= bit;
-            adj[size_t(u) * size_t(nw) + size_t(w >> 6)] |= bit;
-            const uint32_t y = uint32_t(at[size_t(w) * size_t(n) + size_t(u)]) | (uint32_t(w) << 16) | (uint32_t(u) << 24);
-            rec[at[size_t(u) * size_t(n) + size_t(w)]] = uint64_t(uint32_t(x)) | (uint64_t(y) << 32);
+            block[words + at] |= bit;
+            if (g->fwd[size_t(r)] && g->bw[size_t(r)] > 0) block[at] |= bit;
         }
-    std::memcpy(rec + n_rec, row.data(), sizeof(int32_t) * (size_t(n) + 1));
+    const int32_t n_rec = fc_bitrow_lay_down(n, block);
+    if (n_rec < 0) return false;
+    const uint64_t *adj = block.data() + words;
+    uint64_t *rec = block.data() + 2 * words;
+    const int32_t *row = reinterpret_cast<const int32_t *>(rec + n_rec);
+    g->bitrow_adj.assign(adj, adj + words);
+    g->bitrow_row.assign(row, row + n + 1);
+    for (int32_t u = 0; u < n; ++u)
+        for (int32_t r = g->row_ptr[size_t(u)]; r < g->row_ptr[size_t(u) + 1]; ++r)
+            if (g->fwd[size_t(r)]) rec[fc_bitrow_find(adj, row, nw, u, g->other[size_t(r)])] |= uint64_t(uint32_t(g->bw[size_t(r)]));
     *nw_out = nw; *n_rec_out = n_rec;
     return true;
 }

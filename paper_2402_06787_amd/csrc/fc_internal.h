@@ -49,10 +49,13 @@ struct fc_graph {
     bool labels_valid = false;         // d_labels / d_label_hmax may be used
     bool p1_valid = false;             // d_p1 / d_level_off / d_tree_ratio may be used
     // Bit-row tables (graphs of at most 256 vertices): one block {heads [n][nw], adj [n][nw] as 64-bit words; records uint2
-    // [bitrow_rec]; row offsets int32 [n + 1]}, see BitRowGraph.  They follow the bandwidths: fc_graph_update_arcs writes them anew.
+    // [bitrow_rec]; row offsets int32 [n + 1]}, see BitRowGraph.  They follow the bandwidths: fc_graph_update_arcs edits them
+    // in place, and needs the rows of neighbours and the row offsets on the host for it.
     void *d_bitrow = nullptr;
-    int32_t bitrow_nw = 0, bitrow_rec = 0;   // 64-bit words per row, records
-    void *d_edits = nullptr;           // int2 [edits_cap] {record, bandwidth}: staging for fc_graph_update_arcs
+    int32_t bitrow_nw = 0, bitrow_rec = 0;   // 64-bit words per row (0: not usable), records
+    std::vector<uint64_t> bitrow_adj;        // [n * bitrow_nw]
+    std::vector<int32_t> bitrow_row;         // [n + 1]
+    void *d_edits = nullptr;           // int4 [edits_cap]: staging for fc_graph_update_arcs (see fc_update_arcs_kernel)
     size_t edits_cap = 0;
 };
 
@@ -61,8 +64,19 @@ struct fc_graph {
 // bandwidth later) instead of being dropped
 int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const int32_t *head,
                   const int32_t *bandwidth, const uint8_t *is_compute, fc_graph **out, bool keep_zero_links = false);
-// The bit-row tables of g as one block (layout: fc_graph::d_bitrow).  false: g has more than 256 vertices or 65535 records.
-bool fc_host_bitrow(const fc_graph *g, std::vector<uint64_t> &block, int32_t *nw, int32_t *n_rec);
+// The bit-row tables of g as one block (layout: fc_graph::d_bitrow), and g's own copy of the rows of neighbours.  false: g has
+// more than 256 vertices or 65535 records.
+bool fc_host_bitrow(fc_graph *g, std::vector<uint64_t> &block, int32_t *nw, int32_t *n_rec);
+// The records (bandwidth 0) and row offsets behind the rows of neighbours that lie in the second half of `block`, which holds
+// the two sets of rows so far.  Returns the number of records, -1: more than 65535.
+int32_t fc_bitrow_lay_down(int32_t n, std::vector<uint64_t> &block);
+// The record of (x, y); the two are neighbours.
+inline int32_t fc_bitrow_find(const uint64_t *adj, const int32_t *row, int32_t nw, int32_t x, int32_t y) {
+    const uint64_t *a = adj + size_t(x) * size_t(nw);
+    int32_t r = row[x];
+    for (int32_t j = 0; j < (y >> 6); ++j) r += __builtin_popcountll(a[j]);
+    return r + __builtin_popcountll(a[y >> 6] & ((uint64_t(1) << (y & 63)) - 1));
+}
 // Set the bandwidth of existing links on the host side of g (records, in-bandwidths, the facts fc_graph_info reports).
 // Either every update is applied or none; `edits` receives {record, new bandwidth} for both records of every link
 // whose bandwidth changed.

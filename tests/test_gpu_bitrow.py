@@ -109,6 +109,34 @@ def test_updated_links_and_weights_reach_the_bit_rows(n):
         assert (got.cpu().numpy() == o.weighted_aux_maxflow_batch(after, sink, U, k, wts)).all()
 
 
+@pytest.mark.parametrize("n", [2, 64, 65, 129, 256])
+def test_updates_in_place_leave_the_tables_of_a_fresh_upload(n):
+    # all links of one vertex down (bits of one word together) and up again, spare links and single directions of a pair brought
+    # to life, a link listed twice, an update that changes nothing
+    rng = np.random.default_rng(7000 + n)
+    topo = _merge(_random_topology(rng, n, 4))
+    have = set(zip(topo.tail.tolist(), topo.head.tolist()))
+    spares = [(a, b) for a, b in rng.integers(0, n, (2 * n, 2)).tolist() if a != b and (a, b) not in have]
+    cap = dict(zip(zip(topo.tail.tolist(), topo.head.tolist()), topo.bandwidth.tolist()))
+    cap.update({key: 0 for key in spares})
+    keys = sorted(cap)
+    P = 64
+    sink = rng.integers(0, n, P).astype(np.int32); k = rng.integers(1, 6, P).astype(np.int32); U = rng.integers(1, 12, P).astype(np.int32)
+    t, h = ([x[i] for x in keys] for i in (0, 1))
+    with fc.fc_graph_upload_with_spares(n, t, h, [cap[x] for x in keys], topo.is_compute) as g:
+        for change in ([(x, 0) for x in keys if x[0] == 0 or x[1] == n - 1], [(x, 3 + x[1]) for x in keys if x[0] == 0], [(x, 5) for x in spares],
+                       [(keys[0], 9), (keys[0], 2), (keys[-1], cap[keys[-1]])], [(x, int(rng.integers(0, 30))) for x in keys]):
+            if not change:
+                continue
+            fc.fc_graph_update_arcs(g, [x[0] for x, _ in change], [x[1] for x, _ in change], [b for _, b in change], refresh_tables=False)
+            cap.update(dict(change))
+            after = w.Topology("after", n, np.array(t, np.int32), np.array(h, np.int32), np.array([cap[x] for x in keys], np.int32), topo.is_compute)
+            want = o.aux_maxflow_batch(after, sink, U, k, threads=16)
+            for options in (None, {"global_relabel_steps": 32}):
+                got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k), options=options)
+                assert (got.cpu().numpy() == want).all(), (n, options)
+
+
 def _scaled_rail_fabric(boxes, per_box, caps, U):
     """An Eulerian cluster (boxes around a switch, one rail per place in a box) with one bandwidth inside per box, times U."""
     n_compute = boxes * per_box
