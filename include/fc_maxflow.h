@@ -453,14 +453,14 @@ const char *fc_strerror(int code);
  * full; those results are used as far as the guesses turn out right.  A link whose mu was 0 is
  * not tried again while the same root-set grows (its mu cannot rise).  On at most 256 vertices, until the first
  * copy is made and unless an option of the other solver is set, it works the other way round: it grows many trees by the
- * links that no known cut forbids, asks one launch which cuts that breaks, and takes back what does (n_batches then
- * counts the links of every root-set in batches of tree_chain_states).  Otherwise, unless options->tree_warm_start is 2
+ * links that no known cut forbids, asks one launch which cuts that breaks, and takes back what does.  Otherwise, unless options->tree_warm_start is 2
  * the launches do not start from nothing: the flow that brings the other root-sets' demands to a vertex y
  * is kept in device memory (n_vertices rows of one value per link, and as many again per state a launch looks
  * ahead: fewer states are looked ahead when that would exceed 2 GiB), a max-flow into y repairs it for the capacities used
  * up since and then only routes the units that decide mu.  The trees are the same either way.  Output: n_trees
  * root-sets; tree i has root tree_root[i], multiplicity tree_multiplicity[i] (they add up to k per root)
- * and the n_vertices - 1 edges tree_edge_x/y[i * (n_vertices - 1) ..] in the order they were added.
+ * and the n_vertices - 1 edges tree_edge_x/y[i * (n_vertices - 1) ..] in the order they were added.  n_batches_or_null: the
+ * launches it took (none where the cuts left nothing to ask).
  * Needs min over v of F(s, v) >= N k to hold in D* (what switch removal preserves); FC_ENOCONVERGE if no
  * edge can be added.  FC_EWORKSPACE with *n_trees set when tree_capacity is too small. */
 #define FC_MU_INVALID FC_GAMMA_INVALID

@@ -211,7 +211,9 @@ def test_trees_by_cuts_use_every_unit_and_agree_with_the_other_solver(n, k):
     links = w.superposed_out_trees(n, k, 100 + n)
     here = fc.fc_construct_trees(n, links, k)
     there = fc.fc_construct_trees(n, links, k, options={"threads_per_problem": 64})
-    assert here["trees"] == there["trees"]
+    assert here["trees"] == there["trees"] and there["batches"] >= n - 1
+    if all(m == k for _, m, _ in here["trees"]):                                            # no copy: by cuts to the end
+        assert here["batches"] < max(2, n // 4), (here["batches"], there["batches"])
     short = dict(links)
     short[max(short, key=lambda e: (short[e], e))] -= 1                                     # every unit was needed
     for options in (None, {"threads_per_problem": 64}):
@@ -226,3 +228,5 @@ def test_trees_by_cuts_agree_with_the_other_solver_at_the_edges_of_the_row_words
     here = fc.fc_construct_trees(n, links, k)
     there = fc.fc_construct_trees(n, links, k, options={"threads_per_problem": 64})
     assert here["trees"] == there["trees"]
+    if all(m == k for _, m, _ in here["trees"]):                                            # no copy: by cuts to the end
+        assert here["batches"] < n // 4 <= there["batches"], (here["batches"], there["batches"])

@@ -1308,6 +1308,9 @@ def test_tree_mu_batches_match_oracle():
             assert res["mu"].tolist() == want + [fc.FC_MU_INVALID] * 4
 
 
+KEPT = {"threads_per_problem": 64}         # an option of the loop that evaluates state by state: no cuts, whatever the size
+
+
 def test_construct_trees_matches_oracle():
     cases = [(8, o.link_capacities(w.paper_example_split(1)), 1), (8, o.link_capacities(w.paper_example_split(3)), 3),
              (2, {(0, 1): 4, (1, 0): 4}, 4), (4, {(a, b): 3 for a in range(4) for b in range(4) if a != b}, 3),
@@ -1321,10 +1324,11 @@ def test_construct_trees_matches_oracle():
         got = fc.fc_construct_trees(n, links, k)
         assert got["trees"] == want, (n, k)
         _check_trees(n, links, k, got["trees"])
-        assert got["batches"] >= n - 1
-        # every max-flow from nothing instead of from the flows kept between launches: the same trees
-        cold = fc.fc_construct_trees(n, links, k, options={"tree_warm_start": 2})
-        assert cold["trees"] == want and cold["batches"] == got["batches"], (n, k)
+        # one state after the other (KEPT), and every max-flow from nothing instead of from the flows kept between launches: the same trees
+        kept = fc.fc_construct_trees(n, links, k, options=KEPT)
+        assert kept["trees"] == want and kept["batches"] >= n - 1
+        cold = fc.fc_construct_trees(n, links, k, options={**KEPT, "tree_warm_start": 2})
+        assert cold["trees"] == want and cold["batches"] == kept["batches"], (n, k)
     with pytest.raises(fc.FcError) as err:
         fc.fc_construct_trees(2, {(0, 1): 4, (1, 0): 4}, 4, options={"tree_warm_start": 3})
     assert err.value.code == fc.FC_EINVAL
@@ -1343,8 +1347,9 @@ def test_trees_on_superposed_random_out_trees_match_oracle(n, k, seed):
     got = fc.fc_construct_trees(n, links, k)
     assert got["trees"] == want
     assert _check_trees(n, links, k, got["trees"]) == links            # every unit of every link is used
-    cold = fc.fc_construct_trees(n, links, k, options={"tree_warm_start": 2})
-    assert cold["trees"] == want and cold["batches"] == got["batches"]
+    kept = fc.fc_construct_trees(n, links, k, options=KEPT)
+    cold = fc.fc_construct_trees(n, links, k, options={**KEPT, "tree_warm_start": 2})
+    assert kept["trees"] == want and cold["trees"] == want and cold["batches"] == kept["batches"]
 
 
 @pytest.mark.parametrize("n,k,seed", [(48, 3, 11), (96, 1, 12)])
@@ -1354,8 +1359,9 @@ def test_trees_on_larger_superposed_out_trees_use_every_unit(n, k, seed):
     links = w.superposed_out_trees(n, k, seed)
     got = fc.fc_construct_trees(n, links, k)
     assert _check_trees(n, links, k, got["trees"]) == links
-    cold = fc.fc_construct_trees(n, links, k, options={"tree_warm_start": 2})
-    assert cold["trees"] == got["trees"]
+    kept = fc.fc_construct_trees(n, links, k, options=KEPT)
+    cold = fc.fc_construct_trees(n, links, k, options={**KEPT, "tree_warm_start": 2})
+    assert kept["trees"] == got["trees"] and cold["trees"] == got["trees"]
 
 
 def test_trees_on_config1_after_switch_removal_on_the_gpu():
@@ -1433,15 +1439,19 @@ def test_trees_on_config3_after_switch_removal_are_valid():
     assert got["trees"] == want
     # config 3 is symmetric and tight: every unit of every link is used by some tree
     assert sum(use.values()) == len(comp) * k * (len(comp) - 1)
-    assert got["batches"] < len(comp) * (len(comp) - 1)                # the look-ahead saves launches
-    # the flows kept between launches change nothing: same trees as with every max-flow started from nothing
-    cold = fc.fc_construct_trees(len(comp), links, k, options={"tree_warm_start": 2})
-    assert cold["trees"] == got["trees"] and cold["batches"] == got["batches"]
+    # guessing whole trees takes a handful of launches
+    assert got["batches"] <= 8
+    # state by state: the look-ahead saves launches, and the flows kept between launches change nothing
+    kept = fc.fc_construct_trees(len(comp), links, k, options=KEPT)
+    assert kept["trees"] == got["trees"] and len(comp) - 1 <= kept["batches"] < len(comp) * (len(comp) - 1)
+    cold = fc.fc_construct_trees(len(comp), links, k, options={**KEPT, "tree_warm_start": 2})
+    assert cold["trees"] == got["trees"] and cold["batches"] == kept["batches"]
     # how far a launch looks ahead changes the number of launches, never a tree (1: no speculation at all)
     for chain in (1, 5, 64):
-        alt = fc.fc_construct_trees(len(comp), links, k, options={"tree_chain_states": chain})
+        alt = fc.fc_construct_trees(len(comp), links, k, options={**KEPT, "tree_chain_states": chain})
         assert alt["trees"] == got["trees"], chain
-        assert (alt["batches"] > got["batches"]) == (chain < 32), (chain, alt["batches"], got["batches"])
+        assert (alt["batches"] > kept["batches"]) == (chain < 32), (chain, alt["batches"], kept["batches"])
+        assert chain > 1 or alt["batches"] == len(comp) * (len(comp) - 1)
     # first steps of root 0 by the oracle: same edges in the same order
     n = len(comp)
     g = dict(links); sets = [{u} for u in range(n)]; demand = [k] * n
@@ -1513,8 +1523,8 @@ def test_trees_on_config4_sampled_states_replayed_by_the_oracle():
 
 def test_back_end_on_a_rail_fabric_warm_and_cold_and_replayed():
     # 32 boxes x 8 compute nodes, NVSwitch per box, 8 rail switches (the 1024-compute instance of the same generator is the
-    # back end's timing workload): search, switch removal, trees; the trees from kept flows equal the trees with every
-    # max-flow started from nothing; sampled states are replayed by the oracle; D* keeps the optimum
+    # back end's timing workload): search, switch removal, trees; the trees by cuts equal the trees from kept flows and
+    # the trees with every max-flow started from nothing; sampled states are replayed by the oracle; D* keeps the optimum
     topo = w.rail_fabric(32, 8)
     assert o.is_eulerian(topo)
     with _upload(topo) as g:
@@ -1533,8 +1543,10 @@ def test_back_end_on_a_rail_fabric_warm_and_cold_and_replayed():
     warm = fc.fc_construct_trees(n, links, k)
     use = _check_trees(n, links, k, warm["trees"])
     assert sum(use.values()) == n * k * (n - 1)
-    cold = fc.fc_construct_trees(n, links, k, options={"tree_warm_start": 2})
-    assert cold["trees"] == warm["trees"]
+    assert warm["batches"] <= 16                                         # whole trees guessed
+    kept = fc.fc_construct_trees(n, links, k, options=KEPT)
+    cold = fc.fc_construct_trees(n, links, k, options={**KEPT, "tree_warm_start": 2})
+    assert kept["trees"] == warm["trees"] and cold["trees"] == warm["trees"] and cold["batches"] == kept["batches"] > 256
     rng = np.random.default_rng(405)
     samples = [(0, 0), (n - 1, n - 2)] + [(int(rng.integers(0, n)), int(rng.integers(0, n - 1))) for _ in range(10)]
     assert _replay_sampled_states(n, links, k, warm["trees"], samples) >= len(samples)
