@@ -411,7 +411,7 @@ int fc_split_gamma_batch(const fc_graph *g, int32_t U, int32_t k, int64_t n_pair
  * compute-only digraph D* and the path recovery table as rows (u, t, w, amount): `amount` of the capacity of
  * (u, t) was routed through switch w.  *n_out / *n_routes receive the row counts; if a capacity argument is too
  * small the call returns FC_EWORKSPACE with the counts set and nothing else written.  n_batches_or_null counts the
- * launches: on at most 256 vertices, unless an option of the other solver is set, the host splits off what the cuts it
+ * launches: on at most 256 vertices, unless an option of the other solver (or a split_ option) is set, the host splits off what the cuts it
  * knows allow and asks a launch which cuts that breaks; otherwise every batch of gamma max-flows re-uploads the
  * current graph.  Errors: FC_EINVAL (also: D not Eulerian), FC_ENOCONVERGE (an egress link
  * could not be used up: min_v F(s, v) >= N k did not hold in D), FC_EOVERFLOW, FC_EUNSUPPORTED, FC_EDEVICE, FC_ENOMEM. */
@@ -452,8 +452,8 @@ const char *fc_strerror(int code);
  * the first link that was neither rejected before nor zero the last time any root-set tried it is accepted in
  * full; those results are used as far as the guesses turn out right.  A link whose mu was 0 is
  * not tried again while the same root-set grows (its mu cannot rise).  On at most 256 vertices, until the first
- * copy is made and unless an option of the other solver is set, it works the other way round: it grows many trees by the
- * links that no known cut forbids, asks one launch which cuts that breaks, and takes back what does.  Otherwise, unless options->tree_warm_start is 2
+ * copy is made and unless an option of the other solver is set (or tree_warm_start or tree_chain_states, to whatever value),
+ * it works the other way round: it grows many trees by the links that no known cut forbids, asks one launch which cuts that breaks, and takes back what does.  Otherwise, unless options->tree_warm_start is 2
  * the launches do not start from nothing: the flow that brings the other root-sets' demands to a vertex y
  * is kept in device memory (n_vertices rows of one value per link, and as many again per state a launch looks
  * ahead: fewer states are looked ahead when that would exceed 2 GiB), a max-flow into y repairs it for the capacities used

@@ -230,3 +230,14 @@ def test_trees_by_cuts_agree_with_the_other_solver_at_the_edges_of_the_row_words
     assert here["trees"] == there["trees"]
     if all(m == k for _, m, _ in here["trees"]):                                            # no copy: by cuts to the end
         assert here["batches"] < n // 4 <= there["batches"], (here["batches"], there["batches"])
+
+
+def test_tree_options_take_the_loop_that_knows_them():
+    n, k = 24, 1
+    links = _ring_with_chords(n, k)
+    by_cuts = fc.fc_construct_trees(n, links, k)
+    assert all(m == k for _, m, _ in by_cuts["trees"]) and by_cuts["batches"] < n // 2       # no copy
+    runs = {c: fc.fc_construct_trees(n, links, k, options={"tree_chain_states": c}) for c in (1, 4)}
+    runs.update({-v: fc.fc_construct_trees(n, links, k, options={"tree_warm_start": v}) for v in (1, 2)})
+    assert all(r["trees"] == by_cuts["trees"] for r in runs.values())
+    assert runs[1]["batches"] == n * (n - 1) > runs[4]["batches"] > runs[-1]["batches"] == runs[-2]["batches"] >= n
