@@ -137,6 +137,43 @@ def test_updates_in_place_leave_the_tables_of_a_fresh_upload(n):
                 assert (got.cpu().numpy() == want).all(), (n, options)
 
 
+def _spine(boxes, per_box):
+    """Boxes around a box switch, every node on one spine."""
+    n = boxes * per_box
+    t = [c for c in range(n) for _ in (0, 1)]; h = [x for c in range(n) for x in (n + c // per_box, n + boxes)]
+    isc = np.zeros(n + boxes + 1, np.uint8); isc[:n] = 1
+    return w.Topology("spine", len(isc), np.array(t + h, np.int32), np.array(h + t, np.int32), np.tile([9, 2], 2 * n).astype(np.int32), isc)
+
+
+def _regular(n, degree):
+    t = np.repeat(np.arange(n, dtype=np.int32), degree); h = (t + np.tile(np.cumsum(np.arange(1, degree + 1, dtype=np.int32)), n)) % n
+    keep = t != h
+    isc = np.ones(n, np.uint8)
+    return _merge(w.Topology("regular", n, t[keep], h[keep].astype(np.int32), (1 + (t[keep] * 7 + h[keep] * 3) % 50).astype(np.int32), isc))
+
+
+# (fabric, problems that still take the bit rows, problems that are too many for them)
+@pytest.mark.parametrize("name,topo,few,many", [("one word", lambda: _regular(60, 4), 3000, 40000), ("two words", lambda: _regular(120, 6), 2000, 40000),
+                                                ("short rows", lambda: _regular(250, 4), 500, 4000), ("three words", lambda: _regular(180, 4), 1500, 12000),
+                                                ("longer rows", lambda: _regular(180, 7), 5000, 20000), ("long rows", lambda: _regular(250, 14), 1500, 12000),
+                                                ("a spine", lambda: _spine(27, 8), 5000, 60000), ("dense", lambda: _regular(128, 110), 0, 100)])
+def test_the_bit_rows_take_a_batch_where_they_are_ahead(name, topo, few, many):
+    topo = topo()
+    n, comp = topo.n_vertices, np.array(topo.compute_nodes, np.int32)
+    with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for P, bit_rows in ((few, True), (many, False)):
+            if P == 0:
+                continue
+            sink = comp[np.arange(P) % len(comp)]
+            U = np.full(P, 2, np.int32); k = (1 + np.arange(P) // len(comp) % 4).astype(np.int32)
+            flows, st = fc.fc_maxflow_batch(g, _dev(sink), _dev(U), _dev(k), want_stats=True)
+            # (on bit rows every problem searches for heights at least once and nothing is relabeled one by one)
+            assert (st["relabels"] == 0 and st["global_relabels"] >= P) == bit_rows, (name, P, st)
+            one = min(P, 4 * len(comp))                      # the problems repeat from here on
+            assert (flows[:one].cpu().numpy() == o.aux_maxflow_batch(topo, sink[:one], U[:one], k[:one], threads=16)).all()
+            assert torch.equal(flows[:one].repeat(-(-P // one))[:P], flows)
+
+
 def _scaled_rail_fabric(boxes, per_box, caps, U):
     """An Eulerian cluster (boxes around a switch, one rail per place in a box) with one bandwidth inside per box, times U."""
     n_compute = boxes * per_box
