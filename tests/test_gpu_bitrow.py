@@ -220,10 +220,24 @@ def test_switch_removal_by_cuts_agrees_with_the_other_solver(boxes, per_box):
     here = fc.fc_remove_switches(*args, k)
     there = fc.fc_remove_switches(*args, k, options={"split_two_launches": 2})
     assert here["links"] == there["links"] and here["table"] == there["table"]
+    assert 1 < here["batches"] < there["batches"] // 2, (here["batches"], there["batches"])     # by cuts to the end
     for options in (None, {"split_two_launches": 2}):                                       # more than the fabric carries
         with pytest.raises(fc.FcError) as err:
             fc.fc_remove_switches(*args, k + 1, options=options)
         assert err.value.code == fc.FC_ENOCONVERGE
+
+
+def test_a_digraph_too_dense_for_the_chip_goes_to_the_other_solver():
+    # 142 nodes linked to all but one of the others, in a ring by one unit each, the missing unit through a switch: records of 160 KB
+    n = 142
+    t = np.repeat(np.arange(n, dtype=np.int32), n - 2); h = (t + np.tile(np.arange(1, n - 1, dtype=np.int32), n)) % n
+    u = np.arange(n, dtype=np.int32); sw = np.full(n, n, np.int32)
+    isc = np.ones(n + 1, np.uint8); isc[n] = 0
+    args = (n + 1, np.concatenate([t, u, sw]), np.concatenate([h.astype(np.int32), sw, u]), np.ones(len(t) + 2 * n, np.int32), isc, 1)
+    here = fc.fc_remove_switches(*args)
+    there = fc.fc_remove_switches(*args, options={"split_two_launches": 1})
+    assert here["links"] == there["links"] and here["table"] == there["table"] and len(here["table"]) == n
+    assert here["batches"] == there["batches"] >= n
 
 
 def test_a_switch_without_links_is_removed_whatever_the_others_carry():
