@@ -55,8 +55,17 @@ def load_counters():
         return {}
 
 
+def solver_kernel(stats, n_problems):
+    """The kernel that solved a batch, by its counters: on bit rows every problem searches for heights and no vertex is
+    relabeled by itself."""
+    return "fc_bitrow_kernel" if stats["relabels"] == 0 and stats["global_relabels"] >= n_problems else "fc_push_relabel_kernel"
+
+
 def roofline_block(stats, kernel_ms, n_problems, n_src, m_src, hw):
-    """`hw`: {"valu_wave_instructions": .., "hbm_bytes": ..} per launch from profiles/counters.json, or {}."""
+    """`hw`: {"kernel": .., "valu_wave_instructions": .., "hbm_bytes": ..} per launch from profiles/counters.json, or {}."""
+    kernel = solver_kernel(stats, n_problems)
+    if hw.get("kernel") != kernel:
+        hw = {}
     total, init = algorithmic_bytes(stats, n_problems, n_src, m_src)
     sec = kernel_ms * 1e-3
     valu = hw.get("valu_wave_instructions")
@@ -67,7 +76,7 @@ def roofline_block(stats, kernel_ms, n_problems, n_src, m_src, hw):
         "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_GINSTR, "unit": "G wave-instructions/s (vector ALU)",
         "frac": None if achieved is None else achieved / VALU_PEAK_GINSTR,
         "traffic": hbm,
-        "kernel": "fc_push_relabel_kernel", "kernel_ms": kernel_ms,
+        "kernel": kernel, "kernel_ms": kernel_ms,
         "kernel_ms_is": "mean HIP-event time of the solver kernel over launches that write no counters (stats_time_only)",
         "valu_wave_instructions_per_launch": valu,
         "hbm": {
