@@ -56,7 +56,9 @@ extern "C" {
 typedef struct fc_graph fc_graph;                  /* opaque; owned by the library            */
 typedef struct { int64_t num, den; } fc_rational;  /* always reduced, den > 0                  */
 
-/* Work counters summed over the problems of one call (all optional). */
+/* Work counters summed over the problems of one call (all optional).  A batch on a graph of at most 256 vertices may be solved
+ * by the bit-row solver: it relabels no vertex by itself (relabels = 0), searches for heights at least once a problem, counts its
+ * push rounds as level_steps, and in arc_scans the arcs it pushes along or looks at in the rows of single vertices. */
 typedef struct {
     uint64_t pushes;           /* residual-edge updates: one per (arc, push)                          */
     uint64_t relabels;         /* single-vertex height increases by the discharge step                */
