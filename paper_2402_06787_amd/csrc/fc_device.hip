@@ -37,6 +37,7 @@
 #define FC_NSTAT 8   // per-problem counters: pushes, relabels, arc_scans, grs, gr_arc_scans, level_steps, discharges, not_converged
 
 #include "fc_solver_kernels.inc"   // device code
+#include "fc_sink_kernels.inc"     // device code for several problems of each sink
 #include "fc_bitrow_kernels.inc"   // device code for graphs of at most 256 vertices
 #include "fc_launch.inc"           // option defaults, kernel build selection, launches
 #include "fc_api.inc"              // C ABI: graphs, batches, verdicts, searches, edge-splitting batches

@@ -1,0 +1,181 @@
+"""GPU tests of the per-sink solver (batches that ask about every compute node): what one max-flow settles for the other
+candidates of its sink, in every order and with every kind of candidate, against the oracle and against the solver that takes one
+problem at a time."""
+import numpy as np
+import pytest
+
+import oracle as o
+import workloads as w
+
+torch = pytest.importorskip("torch")
+pytestmark = pytest.mark.gpu
+
+if not torch.cuda.is_available():          # selected explicitly on a machine without a GPU
+    pytest.skip("needs a GPU", allow_module_level=True)
+
+import paper_2402_06787_amd as fc   # noqa: E402
+
+DEV = torch.device("cuda:0")
+ALONE = {"global_relabel_steps": 32}       # (its default: an option that only the other solver knows takes the call there)
+
+
+def _dev(a):
+    return torch.from_numpy(np.ascontiguousarray(a, dtype=np.int32)).to(DEV)
+
+
+def _random(n, degree, seed, hub=False, halves=False):
+    """A ring through all vertices (two rings that nothing joins with `halves`) and random arcs, some with the link back."""
+    rng = np.random.default_rng(seed)
+    t, h = [], []
+    for u in range(n):
+        lo, hi = (0, n) if not halves else ((0, n // 2) if u < n // 2 else (n // 2, n))
+        heads = {lo + (u - lo + 1) % (hi - lo)} | set(rng.integers(lo, hi, degree).tolist())
+        if hub and u == 3:
+            heads |= set(range(n))
+        for v in sorted(heads - {u}):
+            t.append(u); h.append(v)
+            if rng.random() < 0.2:
+                t.append(v); h.append(u)
+    isc = np.ones(n, np.uint8)
+    isc[rng.permutation(n)[: n // 10]] = 0
+    return w.Topology(f"r{n}", n, np.array(t, np.int32), np.array(h, np.int32), rng.integers(1, 60, len(t)).astype(np.int32), isc)
+
+
+def _spine(boxes, per_box, seed):
+    """Boxes around a switch, every node with a card to one spine; some cards at half their rate."""
+    rng = np.random.default_rng(seed)
+    N = boxes * per_box
+    t, h, b = [], [], []
+    for u in range(N):
+        for x, bw in ((N + u // per_box, 24), (N + boxes, 1 if rng.random() < 0.05 else 2)):
+            t += [u, x]; h += [x, u]; b += [bw, bw]
+    isc = np.zeros(N + boxes + 1, np.uint8)
+    isc[:N] = 1
+    return w.Topology("spine", N + boxes + 1, np.array(t, np.int32), np.array(h, np.int32), np.array(b, np.int32), isc)
+
+
+TOPOLOGIES = {
+    "few links": lambda: _random(300, 6, 1),                  # heights are searched by links
+    "many links": lambda: _random(620, 8, 2),                 # ... by a queue
+    "257 vertices": lambda: _random(257, 4, 3, hub=True),     # the first size beyond the bit rows; a row longer than any chunk
+    "two halves": lambda: _random(266, 5, 4, halves=True),    # half of the nodes cannot reach a sink: a cut without bandwidth
+    "rails": lambda: w.rail_fabric(36, 8),
+    "spine": lambda: _spine(34, 8, 5),
+}
+
+
+def _in_bw(topo):
+    into = np.zeros(topo.n_vertices, np.int64)
+    np.add.at(into, topo.head, topo.bandwidth)
+    return into[topo.compute_nodes]
+
+
+def _candidates(topo, C, seed, wide=False):
+    """C candidates around the sink cuts' optimum: mixed and equal k, in no order, some twice, some far off, some invalid."""
+    rng = np.random.default_rng(seed)
+    N = topo.n_compute
+    base = N / max(1, int(np.median(_in_bw(topo))))
+    k = np.where(rng.random(C) < 0.5, 6, rng.integers(1, 30, C))
+    if wide:
+        k = k * (70000 // N)                                  # demands on both sides of 65535
+    U = np.maximum(1, (k * base * rng.choice([0.05, 0.5, 0.8, 0.95, 1.0, 1.05, 1.3, 2.0, 6.0], C) * rng.uniform(0.97, 1.03, C)).astype(np.int64))
+    if C >= 9:
+        U[3], k[3] = U[7], k[7]
+        U[5] = 0
+        k[6] = 0
+    return U.astype(np.int32), k.astype(np.int32)
+
+
+def _want(topo, U, k):
+    """[C, N] values, FC_FLOW_INVALID where the candidate is."""
+    comp = topo.compute_nodes
+    ok = (U >= 1) & (k >= 1)
+    want = np.full((len(U), len(comp)), fc.FC_FLOW_INVALID, np.int64)
+    C = int(ok.sum())
+    want[ok] = o.aux_maxflow_batch(topo, np.tile(comp, C).astype(np.int32), np.repeat(U[ok], len(comp)), np.repeat(k[ok], len(comp)), threads=16).reshape(C, len(comp))
+    return want
+
+
+@pytest.mark.parametrize("wide", [False, True])
+@pytest.mark.parametrize("C", [1, 9, 66])
+@pytest.mark.parametrize("name", TOPOLOGIES)
+def test_values_in_every_order(name, C, wide):
+    topo = TOPOLOGIES[name]()
+    comp, N = topo.compute_nodes, topo.n_compute
+    U, k = _candidates(topo, C, 17 * C + wide, wide)
+    want = _want(topo, U, k).reshape(-1)
+    sink, Us, ks = np.tile(comp, C), np.repeat(U, N), np.repeat(k, N)
+    rng = np.random.default_rng(C)
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        alone, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options=ALONE)
+        assert (alone.cpu().numpy() == want).all()
+        orders = {"over and over": np.arange(C * N), "in a row": np.arange(C * N).reshape(C, N).T.reshape(-1), "mixed": rng.permutation(C * N)}
+        for order, perm in orders.items():
+            got, _ = fc.fc_maxflow_batch(g, _dev(sink[perm]), _dev(Us[perm]), _dev(ks[perm]))
+            assert (got.cpu().numpy() == want[perm]).all(), order
+        if not wide:                                          # the caller's bound leaves out the 32-bit state
+            got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options={"src_cap_bound": int(k.max()), "tree_certificate": 1})
+            assert (got.cpu().numpy() == want).all()
+        else:                                                 # and refuses what breaks the promise
+            got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options={"src_cap_bound": 1})
+            over = ks.astype(np.int64) * N > 65535
+            assert (got.cpu().numpy() == np.where(over & (Us >= 1), fc.FC_FLOW_UNSUPPORTED, want)).all()
+        need = k.astype(np.int64) * N
+        for flows in (True, False):
+            r = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=flows)
+            low = want.reshape(C, N) < need[:, None]
+            ok = (U >= 1) & (k >= 1)
+            assert (r["feasible"].cpu().numpy().astype(bool) == (ok & ~low.any(axis=1))).all(), flows
+            assert (r["witness"].cpu().numpy() == np.where(ok & low.any(axis=1), comp[low.argmax(axis=1)], -1)).all(), flows
+            if flows:
+                assert (r["flows"].cpu().numpy().reshape(-1) == want).all()
+
+
+@pytest.mark.parametrize("C", [1, 3, 21])
+@pytest.mark.parametrize("name", TOPOLOGIES)
+def test_rounded_down_capacities(name, C):
+    topo = TOPOLOGIES[name]()
+    comp, N = topo.compute_nodes, topo.n_compute
+    rng = np.random.default_rng(C + 5)
+    base = N / max(1, int(np.median(_in_bw(topo))))
+    den = rng.integers(1, 60, C)
+    k = np.where(rng.random(C) < 0.7, 3, rng.integers(1, 9, C))
+    num = np.maximum(1, (k * den * base * rng.choice([0.3, 0.9, 1.0, 1.1, 1.5, 3.0], C)).astype(np.int64))
+    want = o.aux_maxflow_batch_floor(topo, np.tile(comp, C), np.repeat(num, N), np.repeat(den, N), np.repeat(k, N), threads=16).reshape(C, N)
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        low = want < (k * N)[:, None]
+        for flows in (False, True):
+            r = fc.fc_feasible_floor(g, _dev(num), _dev(den), _dev(k), want_flows=flows)
+            assert (r["feasible"].cpu().numpy().astype(bool) == ~low.any(axis=1)).all(), flows
+            assert (r["witness"].cpu().numpy() == np.where(low.any(axis=1), comp[low.argmax(axis=1)], -1)).all(), flows
+        assert (r["flows"].cpu().numpy() == want).all()
+        got, _ = fc.fc_maxflow_batch_floor(g, _dev(np.tile(comp, C)), _dev(np.repeat(num, N)), _dev(np.repeat(den, N)), _dev(np.repeat(k, N)))
+        assert (got.cpu().numpy().reshape(C, N) == want).all()
+
+
+def test_weights_and_updated_bandwidths():
+    topo = _random(290, 6, 8)
+    comp, N, C = topo.compute_nodes, topo.n_compute, 12
+    rng = np.random.default_rng(9)
+    weights = np.zeros(topo.n_vertices, np.int32)
+    weights[comp] = rng.integers(0, 4, N)
+    U, k = rng.integers(1, 40, C).astype(np.int32), np.full(C, 3, np.int32)
+    sink, Us, ks = np.tile(comp, C), np.repeat(U, N), np.repeat(k, N)
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        # links in both directions at a fraction of their bandwidth, tables rebuilt: what a search by links reads has to follow
+        caps = o.link_capacities(topo)
+        some = sorted(caps)[:: 7]
+        now = {**caps, **{key: max(1, caps[key] // 5) for key in some}}
+        fc.fc_graph_update_arcs(g, [a for a, _ in some], [b for _, b in some], [now[key] for key in some], refresh_tables=True)
+        keys = sorted(now)
+        changed = w.Topology("changed", topo.n_vertices, np.array([a for a, _ in keys], np.int32), np.array([b for _, b in keys], np.int32),
+                             np.array([now[key] for key in keys], np.int32), topo.is_compute)
+        want = o.aux_maxflow_batch(changed, sink, Us, ks, threads=16)
+        got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks))
+        assert (got.cpu().numpy() == want).all()
+        fc.fc_graph_set_source_weights(g, weights)
+        some_p = np.concatenate([np.arange(c * N, c * N + N, 17) for c in range(C)])
+        got, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks))
+        alone, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options=ALONE)
+        assert torch.equal(got, alone)
+        assert (got.cpu().numpy()[some_p] == o.weighted_aux_maxflow_batch(changed, sink[some_p], Us[some_p], ks[some_p], weights)).all()
