@@ -59,6 +59,7 @@ TOPOLOGIES = {
     "many links": lambda: _random(620, 8, 2),                 # ... by a queue
     "257 vertices": lambda: _random(257, 4, 3, hub=True),     # the first size beyond the bit rows; a row longer than any chunk
     "two halves": lambda: _random(266, 5, 4, halves=True),    # half of the nodes cannot reach a sink: a cut without bandwidth
+    "long rows": lambda: _random(280, 24, 6),                 # first arcs are chosen one vertex at a time
     "rails": lambda: w.rail_fabric(36, 8),
     "spine": lambda: _spine(34, 8, 5),
 }
