@@ -56,7 +56,8 @@ extern "C" {
 typedef struct fc_graph fc_graph;                  /* opaque; owned by the library            */
 typedef struct { int64_t num, den; } fc_rational;  /* always reduced, den > 0                  */
 
-/* Work counters summed over the problems of one call (all optional).  A batch on a graph of at most 256 vertices may be solved
+/* Work counters summed over the problems of one call (all optional).  A call that asks for counters solves every problem by itself; one
+ * that does not may let one max-flow settle further candidates of its sink (the same values).  A batch on a graph of at most 256 vertices may be solved
  * by the bit-row solver: it relabels no vertex by itself (relabels = 0), searches for heights at least once a problem, counts its
  * push rounds as level_steps, and in arc_scans the arcs it pushes along or looks at in the rows of single vertices. */
 typedef struct {
