@@ -180,3 +180,32 @@ def test_weights_and_updated_bandwidths():
         alone, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options=ALONE)
         assert torch.equal(got, alone)
         assert (got.cpu().numpy()[some_p] == o.weighted_aux_maxflow_batch(changed, sink[some_p], Us[some_p], ks[some_p], weights)).all()
+
+
+def test_a_cut_too_wide_for_its_product_forbids_nothing():
+    """A minimum cut of 2.1e11 units of bandwidth, none of which carries anything at the smallest multiplier: its bandwidth times the others'
+    numerator is beyond 2^63, and all of them are feasible."""
+    N, S, W = 256, 255, 1 << 23
+    t, h, b = [], [], []
+
+    def link(x, y, bw):
+        t.append(x); h.append(y); b.append(bw)
+    for s in range(S):
+        link(N + s, 0, W)                                     # 255 links that just carry a unit at 1 / 2^23 ...
+        for j in range(100):
+            link(1 + (s + j) % (N - 1), N + s, W - 1)         # ... behind 25 500 that do not
+    for v in range(2, N):                                     # the other nodes are a binary tree
+        link(v, v // 2, W); link(v // 2, v, W)
+    link(0, 1, W)
+    isc = np.zeros(N + S, np.uint8)
+    isc[:N] = 1
+    topo = w.Topology("wide cut", N + S, np.array(t, np.int32), np.array(h, np.int32), np.array(b, np.int32), isc)
+    num, den, k = np.array([1] + [1 << 26] * 7), np.array([W] + [1] * 7), np.ones(8, np.int64)
+    want = o.aux_maxflow_batch_floor(topo, np.tile(topo.compute_nodes, 2), np.repeat(num[:2], N), np.repeat(den[:2], N), np.ones(2 * N, np.int64), threads=16).reshape(2, N)
+    assert want[0, 0] == 1 and (want[1] == N).all()
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for flows in (False, True):
+            r = fc.fc_feasible_floor(g, _dev(num), _dev(den), _dev(k), want_flows=flows)
+            assert r["feasible"].cpu().tolist() == [0] + [1] * 7, flows
+            assert r["witness"].cpu().tolist() == [int(topo.compute_nodes[(want[0] < N).argmax()])] + [-1] * 7, flows
+        assert (r["flows"].cpu().numpy() == want[[0] + [1] * 7]).all()
