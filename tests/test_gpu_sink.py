@@ -209,3 +209,33 @@ def test_a_cut_too_wide_for_its_product_forbids_nothing():
             assert r["feasible"].cpu().tolist() == [0] + [1] * 7, flows
             assert r["witness"].cpu().tolist() == [int(topo.compute_nodes[(want[0] < N).argmax()])] + [-1] * 7, flows
         assert (r["flows"].cpu().numpy() == want[[0] + [1] * 7]).all()
+
+
+@pytest.mark.parametrize("N", [300, 620])                     # heights searched by links, by a queue
+def test_nearly_all_vertices_stuck_on_one_level(N):
+    """Every node is joined to all three switches and to nothing else: all other nodes lie two levels above a sink, and at a small multiplier
+    none of them gets rid of its units by its first arc, or at all.  (The values were right too when the list of the level's vertices could be
+    written over by the vertices left with excess.)"""
+    rng = np.random.default_rng(N)
+    S = 3
+    t, h, b = [], [], []
+    for u in range(N):
+        for x in range(S):
+            t += [u, N + x]; h += [N + x, u]; b += rng.integers(1, 4, 2).tolist()
+    for x in range(S):
+        t.append(N + x); h.append(N + (x + 1) % S); b.append(5)
+    isc = np.zeros(N + S, np.uint8)
+    isc[:N] = 1
+    topo = w.Topology("one level", N + S, np.array(t, np.int32), np.array(h, np.int32), np.array(b, np.int32), isc)
+    comp = topo.compute_nodes
+    U = np.array([1, 2, 9, N // 9, N // 6, N // 5, N // 4, N // 3, N], np.int32)
+    k = np.array([3, 7, 30, 1, 1, 1, 1, 1, 1], np.int32)
+    want = _want(topo, U, k)
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        got, _ = fc.fc_maxflow_batch(g, _dev(np.tile(comp, len(U))), _dev(np.repeat(U, N)), _dev(np.repeat(k, N)))
+        assert (got.cpu().numpy() == want.reshape(-1)).all()
+        for c in range(len(U)):                               # each candidate by itself: no other settles it
+            got, _ = fc.fc_maxflow_batch(g, _dev(comp), _dev(np.repeat(U[c:c + 1], N)), _dev(np.repeat(k[c:c + 1], N)))
+            assert (got.cpu().numpy() == want[c]).all(), c
+        r = fc.fc_feasible(g, _dev(U), _dev(k))
+        assert (r["feasible"].cpu().numpy().astype(bool) == (want == (k.astype(np.int64) * N)[:, None]).all(axis=1)).all()
