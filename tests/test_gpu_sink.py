@@ -239,3 +239,43 @@ def test_nearly_all_vertices_stuck_on_one_level(N):
             assert (got.cpu().numpy() == want[c]).all(), c
         r = fc.fc_feasible(g, _dev(U), _dev(k))
         assert (r["feasible"].cpu().numpy().astype(bool) == (want == (k.astype(np.int64) * N)[:, None]).all(axis=1)).all()
+
+
+@pytest.mark.parametrize("C", [2, 5, 9, 130])
+@pytest.mark.parametrize("name", ["few links", "many links", "spine"])
+def test_lists_in_no_order(name, C):
+    """Lists that are neither the same sinks over and over nor each sink's problems in a row, of sinks that come unequally often: one of them
+    half of the time (more often than a wavefront has lanes), switches, vertices that do not exist; and lists that look ordered but for a few places."""
+    topo = TOPOLOGIES[name]()
+    comp, N, n = topo.compute_nodes, topo.n_compute, topo.n_vertices
+    rng = np.random.default_rng(C)
+    U, k = _candidates(topo, max(C, 3), 5 * C)
+    U, k = U[:C], k[:C]
+    P = C * N
+    sink = rng.integers(0, n, P)                              # any vertex, switches among them
+    sink[rng.random(P) < 0.5] = comp[N // 3]
+    strange = rng.choice(P, 7, replace=False)
+    sink[strange] = [-1, n, n + 5, -2 ** 31, 2 ** 31 - 1, -7, n]
+    nearly = np.tile(comp, C)                                 # over and over, but for a few
+    places = rng.choice(P, 9, replace=False)
+    nearly[places] = rng.integers(-1, n + 1, 9)
+    tail = np.tile(comp, C)                                   # ordered, then not
+    tail[P // 2:] = rng.permutation(tail[P // 2:])
+    rows = np.repeat(comp, C)
+    rows[places] = comp[0]
+    known = {}
+
+    def values(sinks, c):
+        todo = sorted({(int(t), int(x)) for t, x in zip(sinks, c)} - set(known))
+        ok = [(t, x) for t, x in todo if 0 <= t < n and U[x] >= 1 and k[x] >= 1]
+        known.update({q: fc.FC_FLOW_INVALID for q in todo})
+        if ok:
+            got = o.aux_maxflow_batch(topo, np.array([t for t, _ in ok], np.int32), U[[x for _, x in ok]], k[[x for _, x in ok]], threads=16)
+            known.update(zip(ok, got.tolist()))
+        return np.array([known[(int(t), int(x))] for t, x in zip(sinks, c)])
+
+    c = np.repeat(np.arange(C), N)
+    with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for sinks, cand in ((sink, c), (nearly, c), (tail, c), (rows, np.tile(np.arange(C), N)), (sink, rng.integers(0, C, P))):
+            got, _ = fc.fc_maxflow_batch(g, _dev(sinks), _dev(U[cand]), _dev(k[cand]))
+            assert (got.cpu().numpy() == values(sinks, cand)).all()
