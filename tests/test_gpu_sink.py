@@ -279,3 +279,35 @@ def test_lists_in_no_order(name, C):
         for sinks, cand in ((sink, c), (nearly, c), (tail, c), (rows, np.tile(np.arange(C), N)), (sink, rng.integers(0, C, P))):
             got, _ = fc.fc_maxflow_batch(g, _dev(sinks), _dev(U[cand]), _dev(k[cand]))
             assert (got.cpu().numpy() == values(sinks, cand)).all()
+
+
+@pytest.mark.parametrize("bounded", [True, False])            # with the caller's bound one size of flows, without it both
+@pytest.mark.parametrize("C,kinds", [(8, 8), (16, 16), (17, 5), (17, 17), (40, 9), (70, 3), (70, 70), (130, 12)])
+@pytest.mark.parametrize("name", ["few links", "spine", "many links"])
+def test_verdicts_of_rounded_down_capacities_and_many_k(name, C, kinds, bounded):
+    """One or many different k among the candidates: problems of one k share a workgroup, blocks of 64 candidates with more than eight go to the
+    other solver; one block may be of either kind."""
+    topo = TOPOLOGIES[name]()
+    comp, N = topo.compute_nodes, topo.n_compute
+    rng = np.random.default_rng(C + kinds)
+    base = N / max(1, int(np.median(_in_bw(topo))))
+    k = rng.permutation(np.arange(C) % kinds + 1)
+    if C > 64:
+        k[64:] = np.sort(k[64:]) // 4 + 1                     # fewer in the second block
+    if not bounded:
+        k *= 1 + 70000 // (N * kinds)                         # demands on both sides of 65535
+    den = rng.integers(1, 50, C)
+    num = np.maximum(1, (k * den * base * rng.choice([0.4, 0.9, 0.97, 1.0, 1.03, 1.1, 1.6], C)).astype(np.int64))
+    num[C // 2] = 0
+    ok = num >= 1
+    some = np.sort(rng.choice(N, 40, replace=False)) if C > 20 else np.arange(N)      # (the oracle solves one by one)
+    want = o.aux_maxflow_batch_floor(topo, np.tile(comp[some], int(ok.sum())), np.repeat(num[ok], len(some)), np.repeat(den[ok], len(some)),
+                                     np.repeat(k[ok], len(some)), threads=16).reshape(-1, len(some))
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        opts = {"src_cap_bound": int(k.max())} if bounded else {}
+        alone = fc.fc_feasible_floor(g, _dev(num), _dev(den), _dev(k), want_flows=True, options=dict(opts, **ALONE))
+        flows = alone["flows"].cpu().numpy()
+        assert (flows[ok][:, some] == want).all() and (flows[~ok] == fc.FC_FLOW_INVALID).all()
+        for _ in range(2):
+            r = fc.fc_feasible_floor(g, _dev(num), _dev(den), _dev(k), options=opts)
+            assert torch.equal(r["feasible"], alone["feasible"]) and torch.equal(r["witness"], alone["witness"])
