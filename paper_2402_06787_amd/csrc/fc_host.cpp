@@ -67,6 +67,7 @@ int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const
             in_bw[a.h] += a.b; out_bw[a.t] += a.b;
             deg[a.t]++; deg[a.h]++;
             gc = gcd64(gc, a.b); mx = std::max(mx, a.b);
+            g->switches_joined = g->switches_joined || (!g->is_compute[a.t] && !g->is_compute[a.h]);
         }
         int64_t min_in = -1; int32_t eul = 1;
         for (int32_t v = 0; v < n_vertices; ++v) {
