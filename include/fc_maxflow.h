@@ -94,7 +94,9 @@ typedef struct {
     int32_t use_label_table;       /* 1 = on (default), 2 = off: initial exact labels from the
                                       per-sink distance table built at upload                          */
     int32_t force_wide;            /* 1 = always use 32-bit on-chip state (default: 16-bit when it fits) */
-    int32_t max_level_steps;       /* safety cap per problem (default max(100000, 200*|V|))            */
+    int32_t max_level_steps;       /* safety cap per problem (default max(100000, 200*|V|)); set, every problem is
+                                      solved by itself.  The solver that takes a sink at a time, whose
+                                      steps are mostly one vertex, has 16 times the default             */
     int32_t src_cap_bound;         /* > 0: the caller promises k_j <= this for every problem of the call.
                                       If N * bound <= 65535 only the 16-bit-state kernel is launched;
                                       a problem that breaks the promise gets FC_FLOW_UNSUPPORTED        */
