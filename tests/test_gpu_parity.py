@@ -90,6 +90,8 @@ def test_config_flows_match_oracle(cfg):
         bad = np.flatnonzero(got != want)
         assert bad.size == 0, (cfg, bad[:8], got[bad[:8]], want[bad[:8]])
         assert stats["not_converged"] == 0 and stats["pushes"] > 0 and stats["arc_scans"] >= stats["pushes"]
+        plain, _ = _gpu_flows(g, pl.sink, pl.edge_mult, pl.src_cap)      # (without counters one max-flow may settle further candidates)
+        assert (plain == want).all()
         # bounds that hold for any correct value: k <= F <= min(N k, k + U B^-(v))
         Bin = np.asarray(o.in_bandwidths(topo), dtype=np.int64)
         k64 = pl.src_cap.astype(np.int64); U64 = pl.edge_mult.astype(np.int64)
@@ -273,14 +275,17 @@ def test_repeated_calls_reorder_but_do_not_change_values():
     want = o.aux_maxflow_batch(topo, pl.sink, pl.edge_mult, pl.src_cap, threads=16)
     rng = np.random.default_rng(11)
     with _upload(topo) as g:
+        # (the launch is ordered by the solver of single problems, which an option that only it knows chooses; the plain calls beside it)
+        single = {"global_relabel_steps": 32}
         for rep in range(3):
             perm = rng.permutation(pl.n_problems)
-            got, _ = _gpu_flows(g, pl.sink[perm], pl.edge_mult[perm], pl.src_cap[perm])
-            assert (got == want[perm]).all(), rep
+            for options in (single, None):
+                got, _ = _gpu_flows(g, pl.sink[perm], pl.edge_mult[perm], pl.src_cap[perm], options=options)
+                assert (got == want[perm]).all(), (rep, options)
         U, k = config_candidates(5, inv)
-        first = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=True)["flows"].cpu().numpy()
-        again = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=True, options={"schedule": 2})["flows"].cpu().numpy()
-        assert (first == again).all() and (first.reshape(-1) == want).all()
+        for options in (single, dict(single, schedule=2), None, {"schedule": 2}):
+            flows = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=True, options=options)["flows"].cpu().numpy()
+            assert (flows.reshape(-1) == want).all(), options
 
 
 # ------------------------------------------------------------------ edge cases of the boundary

@@ -311,3 +311,64 @@ def test_verdicts_of_rounded_down_capacities_and_many_k(name, C, kinds, bounded)
         for _ in range(2):
             r = fc.fc_feasible_floor(g, _dev(num), _dev(den), _dev(k), options=opts)
             assert torch.equal(r["feasible"], alone["feasible"]) and torch.equal(r["witness"], alone["witness"])
+
+
+@pytest.mark.parametrize("n,degree,back", [(1400, 2, 0.0), (1300, 6, 0.2), (3000, 5, 0.2)])
+def test_more_vertices_than_the_registers_hold(n, degree, back):
+    """Set-up keeps 1024 labels and 1280 first-pass entries a problem in registers and takes the rest one by one; 2800 links are searched link by
+    link, the others by a queue."""
+    rng = np.random.default_rng(n)
+    t, h = [], []
+    for u in range(n):
+        for v in sorted(({(u + 1) % n} | set(rng.integers(0, n, degree - 1).tolist())) - {u}):
+            t.append(u); h.append(v)
+            if rng.random() < back:
+                t.append(v); h.append(u)
+    isc = np.zeros(n, np.uint8)
+    isc[rng.permutation(n)[:130]] = 1
+    topo = w.Topology(f"large{n}", n, np.array(t, np.int32), np.array(h, np.int32), rng.integers(1, 60, len(t)).astype(np.int32), isc)
+    comp, N, C = topo.compute_nodes, topo.n_compute, 5
+    U, k = _candidates(topo, C, n)
+    k[C - 1] = 70000 // N                                     # one demand beyond 65535
+    U[C - 1] = U[C - 1] * 50
+    want = _want(topo, U, k)
+    perm = rng.permutation(C * N)
+    sink, Us, ks = np.tile(comp, C), np.repeat(U, N), np.repeat(k, N)
+    with fc.fc_graph_upload(n, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for p in (np.arange(C * N), perm):
+            got, _ = fc.fc_maxflow_batch(g, _dev(sink[p]), _dev(Us[p]), _dev(ks[p]))
+            assert (got.cpu().numpy() == want.reshape(-1)[p]).all()
+        r = fc.fc_feasible(g, _dev(U), _dev(k))
+        assert (r["feasible"].cpu().numpy().astype(bool) == (want == (k.astype(np.int64) * N)[:, None]).all(axis=1)).all()
+
+
+def test_demands_of_both_sizes_in_two_launches():
+    """10 500 links: the state with 32-bit flows fits a CU three times and the one with 16-bit flows four times, and 450 sinks need more places
+    than that, so each size of demand has a launch of its own.  Candidates of one sink lie on both sides of 65535."""
+    topo = _random(500, 17, 12)
+    comp, N, C = topo.compute_nodes, topo.n_compute, 12
+    assert N == 450 and 9000 < topo.n_arcs < 11000
+    rng = np.random.default_rng(31)
+    base = N / max(1, int(np.median(_in_bw(topo))))
+    k = rng.permutation(np.array([1, 3, 20, 144, 145, 146, 147, 160, 200, 400, 145, 146]))      # 145 * 450 = 65250, 146 * 450 = 65700
+    U = np.maximum(1, (k * base * rng.choice([0.6, 0.95, 1.0, 1.05, 1.4], C)).astype(np.int64)).astype(np.int32)
+    k = k.astype(np.int32)
+    want = _want(topo, U, k)
+    need = k.astype(np.int64) * N
+    assert (need <= 65535).sum() >= 4 and (need > 65535).sum() >= 4
+    sink, Us, ks = np.tile(comp, C), np.repeat(U, N), np.repeat(k, N)
+    low = want < need[:, None]
+    with fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute) as g:
+        for p in (np.arange(C * N), np.arange(C * N).reshape(C, N).T.reshape(-1), rng.permutation(C * N)):
+            got, _ = fc.fc_maxflow_batch(g, _dev(sink[p]), _dev(Us[p]), _dev(ks[p]))
+            assert (got.cpu().numpy() == want.reshape(-1)[p]).all()
+        for flows in (True, False):
+            r = fc.fc_feasible(g, _dev(U), _dev(k), want_flows=flows)
+            assert (r["feasible"].cpu().numpy().astype(bool) == ~low.any(axis=1)).all(), flows
+            assert (r["witness"].cpu().numpy() == np.where(low.any(axis=1), comp[low.argmax(axis=1)], -1)).all(), flows
+            if flows:
+                assert (r["flows"].cpu().numpy() == want).all()
+        # the same capacities as rational multipliers
+        r = fc.fc_feasible_floor(g, _dev(U.astype(np.int64) * 3), _dev(np.full(C, 3)), _dev(k))
+        assert (r["feasible"].cpu().numpy().astype(bool) == ~low.any(axis=1)).all()
+        assert (r["witness"].cpu().numpy() == np.where(low.any(axis=1), comp[low.argmax(axis=1)], -1)).all()

@@ -33,12 +33,14 @@ def test_static_scratch_entry_point_matches_the_workspace_one():
         for idx in (first, second, third):
             sink, U, k = _dev(pl.sink[idx]), _dev(pl.edge_mult[idx]), _dev(pl.src_cap[idx])
             want, _ = fc.fc_maxflow_batch(g, sink, U, k)
-            out = torch.full((len(idx),), -77, dtype=torch.int32, device=DEV)
-            before = torch.cuda.memory_stats(DEV)["allocation.all.allocated"]      # allocations so far (never goes down)
-            got = fc.fc_maxflow_batch_static(g, sink, U, k, out)
-            assert torch.cuda.memory_stats(DEV)["allocation.all.allocated"] == before   # the binding asked torch for nothing
-            torch.cuda.synchronize()
-            assert torch.equal(got, want), int((got != want).sum())
+            # the solver of single problems, whose launch order the static array holds (an option that only it knows), and the plain call
+            for options in ({"global_relabel_steps": 32}, None):
+                out = torch.full((len(idx),), -77, dtype=torch.int32, device=DEV)
+                before = torch.cuda.memory_stats(DEV)["allocation.all.allocated"]      # allocations so far (never goes down)
+                got = fc.fc_maxflow_batch_static(g, sink, U, k, out, options=options)
+                assert torch.cuda.memory_stats(DEV)["allocation.all.allocated"] == before   # the binding asked torch for nothing
+                torch.cuda.synchronize()
+                assert torch.equal(got, want), int((got != want).sum())
             if len(idx) <= 1500:
                 ref = o.aux_maxflow_batch(topo, pl.sink[idx], pl.edge_mult[idx], pl.src_cap[idx], threads=16)
                 assert (got.cpu().numpy().astype(np.int64) == ref).all()
