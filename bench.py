@@ -10,12 +10,18 @@ Section 5.2.  The topology is uploaded once, outside the timed region (its cost 
 through `fc_feasible` (candidate x sink grid + the verdict reduction of Theorem 1) are timed beside it,
 and so are the four smaller configurations.
 
-Prints ONE JSON line.  Every figure quoted in README.md can be re-derived from it:
-  value, ms_per_step            whole-step wall time over the timed region
-  roofline                      the dominant kernel against the vector-issue roof that binds it, with the
-                                algorithmic-bytes rate (with and without the per-problem init term) and the
-                                HBM traffic the hardware counters measured beside it
-  configs                       configs 1-4: solves/s for both entry points, counters, kernel time
+Prints ONE JSON line:
+  value, ms_per_step            whole-step wall time over the timed region.  A solve is one (sink, candidate) problem whose
+                                value the call returns.  On graphs beyond the bit rows a max-flow whose demand arrives in
+                                full, or whose minimum cut is met again at another candidate, settles further problems of
+                                its sink (exactly), so that fewer max-flows are run than problems are solved
+  kernel, kernel_ms, roofline   the kernel of that step: its time, and vector instructions and HBM bytes of the hardware
+                                counters (profiles/) over it
+  every_problem_by_itself       the same step by the solver that runs one max-flow a problem, and what it counted:
+                                residual-edge updates, arc scans, its own roofline with the algorithmic-bytes rate (with
+                                and without the per-problem init term).  Absent where the step's kernel is of that kind:
+                                its counters then stand beside `kernel`
+  configs                       configs 1-4: the same for both entry points, without the counters
   graph_upload_ms, search       ingest + per-sink tables, and the optimality search on top of it
   cpu_baseline, parity_vs_oracle
 """
@@ -55,42 +61,46 @@ def load_counters():
         return {}
 
 
-def solver_kernel(stats, n_problems):
-    """The kernel that solved a batch, by its counters: on bit rows every problem searches for heights and no vertex is
-    relabeled by itself."""
+def counting_kernel(stats, n_problems):
+    """The kernel that solved a batch whose work was counted, by its counters: on bit rows every problem searches for
+    heights and no vertex is relabeled by itself."""
     return "fc_bitrow_kernel" if stats["relabels"] == 0 and stats["global_relabels"] >= n_problems else "fc_push_relabel_kernel"
 
 
-def roofline_block(stats, kernel_ms, n_problems, n_src, m_src, hw):
-    """`hw`: {"kernel": .., "valu_wave_instructions": .., "hbm_bytes": ..} per launch from profiles/counters.json, or {}."""
-    kernel = solver_kernel(stats, n_problems)
-    if hw.get("kernel") != kernel:
-        hw = {}
-    total, init = algorithmic_bytes(stats, n_problems, n_src, m_src)
+def roofline_block(kernel, kernel_ms, hw, stats=None, n_problems=0, n_src=0, m_src=0):
+    """`hw`: {kernel: {"valu_wave_instructions": .., "hbm_bytes": ..}} per launch from profiles/counters.json, or {}.  With the
+    work counted (`stats`) the algorithmic bytes too: what a plain 32-bit in-memory layout would move for that work; the kernels
+    keep the state in LDS, so the measured HBM traffic is a small fraction of it.  kernel_ms: mean HIP-event time of the solver
+    kernel over launches that write no counters."""
+    hw = hw.get(kernel, {})
     sec = kernel_ms * 1e-3
     valu = hw.get("valu_wave_instructions")
     hbm = hw.get("hbm_bytes")
     achieved = None if valu is None else valu / sec / 1e9
-    return {
-        # what binds the kernel (counters in profiles/): instruction issue, not memory -- all per-problem state is in LDS
-        "bound": "alu", "achieved": achieved, "peak": VALU_PEAK_GINSTR, "unit": "G wave-instructions/s (vector ALU)",
-        "frac": None if achieved is None else achieved / VALU_PEAK_GINSTR,
-        "traffic": hbm,
-        "kernel": kernel, "kernel_ms": kernel_ms,
-        "kernel_ms_is": "mean HIP-event time of the solver kernel over launches that write no counters (stats_time_only)",
-        "valu_wave_instructions_per_launch": valu,
-        "hbm": {
-            "note": "algorithmic bytes = what a plain 32-bit in-memory layout would move for the counted work; the kernel "
-                    "keeps that state in LDS, so measured HBM traffic is a small fraction of it",
-            "algorithmic_bytes_per_launch": int(total), "algorithmic_init_bytes": int(init),
-            "algorithmic_gbs": total / sec / 1e9, "algorithmic_frac_of_peak": total / sec / 1e9 / HBM_PEAK_GBS,
-            "algorithmic_frac_without_init": (total - init) / sec / 1e9 / HBM_PEAK_GBS,
-            "measured_bytes_per_launch": hbm,
-            "measured_gbs": None if hbm is None else hbm / sec / 1e9,
-            "measured_frac_of_peak": None if hbm is None else hbm / sec / 1e9 / HBM_PEAK_GBS,
-            "peak_gbs": HBM_PEAK_GBS,
-        },
+    block = {
+        # (no memory bound: all per-problem state is in LDS.  The kernels of single problems are bound by instruction issue, the
+        # per-sink one by its longest chain of dependent steps)
+        "bound": "latency" if kernel == "fc_sink_kernel" else "alu",
+        "achieved": achieved, "peak": VALU_PEAK_GINSTR, "unit": "G wave-instructions/s (vector ALU)",
+        "frac": None if achieved is None else achieved / VALU_PEAK_GINSTR, "traffic": hbm,
+        "hbm_gbs": None if hbm is None else hbm / sec / 1e9,
+        "hbm_frac_of_peak": None if hbm is None else hbm / sec / 1e9 / HBM_PEAK_GBS,
     }
+    if stats:
+        total, init = algorithmic_bytes(stats, n_problems, n_src, m_src)
+        block.update(algorithmic_bytes=int(total), algorithmic_init_bytes=int(init), algorithmic_gbs=total / sec / 1e9,
+                     algorithmic_frac_of_peak=total / sec / 1e9 / HBM_PEAK_GBS,
+                     algorithmic_frac_without_init=(total - init) / sec / 1e9 / HBM_PEAK_GBS)
+    return block
+
+
+def short(x):
+    """Six significant digits: the line stays short enough to be kept whole."""
+    if isinstance(x, float):
+        return float(f"{x:.6g}")
+    if isinstance(x, dict):
+        return {k: short(v) for k, v in x.items()}
+    return [short(v) for v in x] if isinstance(x, (list, tuple)) else x
 
 
 def _cpu_model():
@@ -169,8 +179,8 @@ def main():
         torch.cuda.synchronize()
         return (time.perf_counter() - t0) / steps
 
-    def measure_config(cfg, steps, warmup, want=("batch", "feasible")):
-        """Upload, search, and time both entry points on one configuration's problem list."""
+    def measure_config(cfg, steps, warmup, want=("batch", "feasible"), full=True):
+        """Upload, search, and time both entry points on one configuration's problem list.  `full`: with what the solver counted."""
         topo = w.config_topology(cfg)
         t0 = time.perf_counter()
         g = fc.fc_graph_upload(topo.n_vertices, topo.tail, topo.head, topo.bandwidth, topo.is_compute)
@@ -207,11 +217,11 @@ def main():
                                            options=dict(opts, **kw.pop("o", {})), **kw)
         res = {"config": cfg, "workload": f"{w.CONFIG_NAMES[cfg]}: {N} sinks x {C} candidates = {P} max-flows per step "
                                           f"(|V|={topo.n_vertices}, merged arcs={info.n_arcs_merged}, k={int(ck[0])}, "
-                                          f"U={int(cU[0])}..{int(cU[-1])}, 1/x*={inv[0]}/{inv[1]})",
+                                          f"U={int(cU[0])}..{int(cU[-1])}, 1/x*={inv[0]}/{inv[1]})" if full else w.CONFIG_NAMES[cfg],
                "problems_per_step": P, "graph_upload_ms": upload_ms, "graph_upload_and_free_again_ms": upload_again_ms,
-               "search": {"inv_xstar": f"{inv[0]}/{inv[1]}", "U": str(search["U"]), "k": search["k"], "rounds": search["rounds"],
-                          "candidates_tested": search["trace_len"], "wall_ms": search_ms, "first_call_wall_ms": search_first_ms,
-                          "incl_upload_ms": upload_ms + search_ms}}
+               "search": {"inv_xstar": f"{inv[0]}/{inv[1]}", "U": str(search["U"]), "k": search["k"], "rounds": search["rounds"], "wall_ms": search_ms}}
+        if full:
+            res["search"].update(candidates_tested=search["trace_len"], first_call_wall_ms=search_first_ms, incl_upload_ms=upload_ms + search_ms)
         for name, fn in (("batch", batch), ("feasible", feas)):
             if name not in want:
                 continue
@@ -223,10 +233,12 @@ def main():
             r = fn(want_stats=True)                          # one launch that counts its work: every problem is solved by itself
             st = r[1] if name == "batch" else r["stats"]
             kernel_ms = float(np.mean(kms))
-            # The plain call lets one max-flow settle the other candidates of its sink (graphs beyond the bit rows; see the note).  The
-            # counters, and the roofline that they belong to, are those of the solver that takes one problem at a time, timed here.
-            alone, alone_ms, alone_step = None, kernel_ms, per_step
-            if solver_kernel(st, P) != "fc_bitrow_kernel":
+            counting = counting_kernel(st, P)
+            # a plain call of eight candidates and more on a graph beyond the bit rows goes to the per-sink solver; the one that
+            # takes a problem at a time is timed beside it
+            kernel = counting if counting == "fc_bitrow_kernel" else "fc_sink_kernel"
+            alone_ms, alone_step = kernel_ms, per_step
+            if kernel != counting:
                 alone = {"global_relabel_steps": 32}         # (its default: an option that only that solver knows)
                 alone_step = timed(lambda: fn(o=alone), warmup, steps)
                 ams = []
@@ -238,17 +250,18 @@ def main():
                 fn()                                         # the cost hints as the plain path leaves them
             entry = "fc_maxflow_batch" if name == "batch" else "fc_feasible"
             hw = hw_all.get(f"cfg{cfg}", {}).get(entry, {})
-            res[entry] = {"value": P / per_step, "unit": "solves/s", "ms_per_step": per_step * 1e3,
-                          "kernel_ms": kernel_ms, "kernel_ms_counting_launch": st["device_ms"],
-                          "residual_edge_updates_per_sec": st["pushes"] / (alone_ms * 1e-3),
-                          "arc_scans_per_sec": st["arc_scans"] / (alone_ms * 1e-3),
-                          "per_launch": {k: int(v) for k, v in st.items() if k != "device_ms"},
-                          "roofline": roofline_block(st, alone_ms, P, n_src, m_src, hw)}
-            if alone:
-                res[entry]["note"] = ("value: flow values per second of the plain call, in which a max-flow whose demand arrives in full, or whose minimum "
-                                      "cut is met again at another candidate, settles further candidates of its sink (exact); counters, edge updates "
-                                      "and roofline: the solver that takes every problem by itself")
-                res[entry]["every_problem_by_itself"] = {"value": P / alone_step, "unit": "solves/s", "ms_per_step": alone_step * 1e3, "kernel_ms": alone_ms}
+            counted = {"residual_edge_updates_per_sec": st["pushes"] / (alone_ms * 1e-3), "arc_scans_per_sec": st["arc_scans"] / (alone_ms * 1e-3)}
+            if full and name == want[0]:                     # (the headline's entry point)
+                counted.update(per_launch={k: int(v) for k, v in st.items() if k != "device_ms"},
+                               roofline=roofline_block(counting, alone_ms, hw, st, P, n_src, m_src))
+            res[entry] = {"value": P / per_step, "unit": "solves/s", "ms_per_step": per_step * 1e3, "kernel": kernel, "kernel_ms": kernel_ms}
+            if kernel == counting:
+                res[entry].update(counted)
+            else:
+                if full:
+                    res[entry]["roofline"] = roofline_block(kernel, kernel_ms, hw)
+                res[entry]["every_problem_by_itself"] = dict({"value": P / alone_step, "ms_per_step": alone_step * 1e3,
+                                                              "kernel": counting, "kernel_ms": alone_ms}, **counted)
         handles = dict(g=g, topo=topo, info=info, N=N, P=P, C=C, cU=cU, ck=ck, pl=pl, opts=opts, d_U=d_U, d_k=d_k, ws_f=ws_f,
                        feas=feas, batch=batch, d_out=d_out, d_sink=d_sink, d_mult=d_mult, d_cap=d_cap, ws_b=ws_b)
         return res, handles
@@ -273,15 +286,10 @@ def main():
         "higher_is_better": True, "scaling": "weak", "vs_baseline": None, "dtype": "int32",
         "data": "synthetic",
         "config": {"workload": head["workload"], "entry_point": entry_point, "problems_per_step": P},
-        "residual_edge_updates_per_sec": main_leg["residual_edge_updates_per_sec"],
-        "arc_scans_per_sec": main_leg["arc_scans_per_sec"],
-        "kernel_ms": main_leg["kernel_ms"],
-        "every_problem_by_itself": main_leg.get("every_problem_by_itself"), "note": main_leg.get("note"),
-        "per_launch": main_leg["per_launch"],
-        "roofline": main_leg["roofline"],
+        "note": "a solve is a (sink, candidate) problem whose value the call returns; a max-flow may settle several",
+        **{k: v for k, v in main_leg.items() if k not in ("value", "unit", "ms_per_step")},
         "fc_feasible": head.get("fc_feasible") if entry_point != "fc_feasible" else None,
         "graph_upload_ms": head["graph_upload_ms"], "graph_upload_and_free_again_ms": head["graph_upload_and_free_again_ms"],
-        "graph_upload_is": "fc_graph_upload: validation, merging, residual CSR on the host, copies, per-sink label / first-arc tables by a kernel on the device",
         "search": head["search"],
     }
 
@@ -291,7 +299,7 @@ def main():
         for c in (1, 2, 3, 4):
             if c == cfg:
                 continue
-            r, h = measure_config(c, max(10, args.steps), max(3, args.warmup // 2))
+            r, h = measure_config(c, max(10, args.steps), max(3, args.warmup // 2), full=False)
             h["g"].close()
             out["configs"].append(r)
 
@@ -299,7 +307,7 @@ def main():
         # N*k units are answered without running the solver); reported beside the headline, never as it
         el = timed(lambda: H["feas"](o={"tree_certificate": 1}), args.warmup, args.steps)
         out["with_tree_certificate"] = {"value": P / el, "unit": "solves/s", "ms_per_step": el * 1e3,
-                                        "note": "fc_feasible with option tree_certificate=1; not the headline"}
+                                        "note": "fc_feasible with option tree_certificate=1"}
         for _ in range(3):                               # restore the cost hints the plain path leaves
             H["feas"]()
         torch.cuda.synchronize()
@@ -378,9 +386,7 @@ def main():
         el = timed(lambda: fc.fc_split_gamma_batch(g3, U3, k3, *d3, d_workspace=ws3), 3, reps)
         P3 = 256 * 2 * t3.n_compute
         gamma = {"workload": f"{w.CONFIG_NAMES[3]} scaled by U={U3}, k={k3}: 256 pairs per step, gamma of each from the theorem's 2N = {2 * t3.n_compute} max-flows",
-                 "value": 256 / el, "unit": "pairs/s", "ms_per_step": el * 1e3,
-                 "note": "gamma only: the 2N max-flows of a pair are two types that differ in one sink, the compute node v; one max-flow per pair "
-                         "and type without v is solved (512 a step), and one per v only where that one leaves gamma open"}
+                 "value": 256 / el, "unit": "pairs/s", "ms_per_step": el * 1e3}
         el = timed(lambda: fc.fc_split_gamma_batch(g3, U3, k3, *d3, want_flows=True, d_workspace=ws3), 3, reps)
         gamma["with_exact_flows"] = {"value": P3 / el, "unit": "flow values/s", "flow_values": P3, "ms_per_step": el * 1e3}
         if not args.no_cpu_baseline:
@@ -466,7 +472,7 @@ def main():
         out["parity_vs_oracle"] = {"checked": int(len(idx)), "mismatches": int((gpu_flows[idx] != ref).sum()),
                                    "mismatches_fc_maxflow_batch": int((batch_flows[idx] != ref).sum())}
     g.close()
-    print(json.dumps(out), flush=True)
+    print(json.dumps(short(out), separators=(",", ":")), flush=True)
 
 
 if __name__ == "__main__":
