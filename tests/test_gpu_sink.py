@@ -65,6 +65,11 @@ TOPOLOGIES = {
 }
 
 
+def _merged(topo):
+    tail, head, bw = o.links(topo)
+    return w.Topology(topo.name, topo.n_vertices, tail, head, bw, topo.is_compute)
+
+
 def _in_bw(topo):
     into = np.zeros(topo.n_vertices, np.int64)
     np.add.at(into, topo.head, topo.bandwidth)
@@ -180,6 +185,17 @@ def test_weights_and_updated_bandwidths():
         alone, _ = fc.fc_maxflow_batch(g, _dev(sink), _dev(Us), _dev(ks), options=ALONE)
         assert torch.equal(got, alone)
         assert (got.cpu().numpy()[some_p] == o.weighted_aux_maxflow_batch(changed, sink[some_p], Us[some_p], ks[some_p], weights)).all()
+        # verdicts of rounded-down capacities: what a cut forbids counts the weights on the sink's side
+        total = int(weights.sum())
+        kk = np.array([1, 2, 2, 2, 2, 2, 2, 2, 3, 3, 3, 2], np.int32)
+        num = np.maximum(1, (kk * 7 * total / _in_bw(changed).min() * np.linspace(0.2, 4.0, C)).astype(np.int64))
+        args = _dev(num), _dev(np.full(C, 7)), _dev(kk)
+        r, single = fc.fc_feasible_floor(g, *args), fc.fc_feasible_floor(g, *args, want_flows=True, options=ALONE)
+        assert torch.equal(r["feasible"], single["feasible"]) and torch.equal(r["witness"], single["witness"])
+        assert (single["flows"].cpu().numpy() < (kk.astype(np.int64) * total)[:, None]).any(axis=1).any() and single["feasible"].any()
+        some_n = np.arange(0, N, 29)
+        ref = o.weighted_aux_maxflow_batch(_merged(changed), np.tile(comp[some_n], C), np.repeat(num, len(some_n)), np.repeat(kk, len(some_n)), weights, U_den=np.full(C * len(some_n), 7))
+        assert (single["flows"].cpu().numpy()[:, some_n].reshape(-1) == ref).all()
 
 
 def test_a_cut_too_wide_for_its_product_forbids_nothing():
