@@ -67,7 +67,6 @@ int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const
             in_bw[a.h] += a.b; out_bw[a.t] += a.b;
             deg[a.t]++; deg[a.h]++;
             gc = gcd64(gc, a.b); mx = std::max(mx, a.b);
-            g->switches_joined = g->switches_joined || (!g->is_compute[a.t] && !g->is_compute[a.h]);
         }
         int64_t min_in = -1; int32_t eul = 1;
         for (int32_t v = 0; v < n_vertices; ++v) {
@@ -99,6 +98,9 @@ int fc_host_build(int32_t n_vertices, int64_t n_arcs, const int32_t *tail, const
             int32_t r = fill[arcs[i].h]++;
             g->other[r] = arcs[i].t; g->pair[r] = int32_t(i); g->bw[r] = int32_t(arcs[i].b); g->fwd[r] = 0;
         }
+        for (int32_t v = 0; v < n_vertices && !g->switches_joined; ++v)
+            for (int32_t r = g->row_ptr[v]; !g->is_compute[v] && r < g->row_ptr[v + 1]; ++r)
+                g->switches_joined = g->switches_joined || !g->is_compute[g->other[r]];
         *out = g;
         return FC_OK;
     } catch (const std::bad_alloc &) {

@@ -32,7 +32,7 @@ struct fc_graph {
     int device = -1;
     int32_t *d_row_ptr = nullptr;      // [n+1]
     void *d_arc_wide = nullptr;        // int4 [2*m0]: {other, pair, bw, fwd}
-    void *d_arc_compact = nullptr;     // uint2 [2*m0]: {other | fwd<<15 | pair<<16, bw}; null if ids do not fit 15 bits
+    void *d_arc_compact = nullptr;     // uint2 [max(1, 2*m0) + m0]: records {other | fwd<<15 | pair<<16, bw}, then links by number {tail | head<<16, bw}; null if ids do not fit
     uint8_t *d_is_compute = nullptr;   // [n]
     int32_t *d_compute_ids = nullptr;  // [N]
     int32_t *d_in_bw = nullptr;        // [n]
